@@ -65,8 +65,8 @@ typedef enum {
  *   e = 2i, 2i+1) in byte i % 4, low nibble for i < 4 and high nibble for i >= 4.  Size N*K/4 bytes.
  *
  * Integer-weight layouts (Appendix "Insight", Table 3, Algorithm "ELUT mpGEMM"): weights from a set of C consecutive
- * integers, packed from int8 values with bitnet_pack_int_weights and multiplied by table lookups (Eq. 3, with the
- * sign operation of Eq. 5 where the set is symmetric).  Row-major planes; group j of row n is weights g j .. g j+g-1.
+ * integers, packed from int8 values with bitnet_pack_int_weights; the accumulators are the sums of the table lookups of
+ * Eq. 3 (with the sign operation of Eq. 5 where the set is symmetric), formed as int8 matrix products.  Row-major planes; group j of row n is weights g j .. g j+g-1.
  * BITNET_LAYOUT_C4G2: C = 4 {-2, -1, 0, 1}, g = 2, code 4 (w0 + 2) + (w1 + 2) in 4 bits (group j in byte
  *   n K/4 + j/2, low nibble first); 2 bits per weight.  Size N*K/4.
  * BITNET_LAYOUT_C5G2: C = 5 {-2, .., 2}, g = 2, 4-bit index |5 w0 + w1| placed as C4G2's codes, then a sign plane
@@ -159,8 +159,8 @@ size_t bitnet_mpgemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K
  *   small-batch regime between decode and prefill, which the paper leaves open, Sec. "Limitations"); larger M the
  *   prefill GEMM.  TL1: the same decode GEMV (the pair codes expanded to int8 in registers) where I2_S runs it;
  *   otherwise the weights are rewritten in the I2_S layout in the workspace (N * K / 4 bytes) for the prefill GEMM.
- *   Integer-weight layouts (C4G2, C5G2, C3G5): table lookups with the tables built in LDS for 4 tokens at a time
- *   (2 for C3G5), any M; x_rowsum is not used and no workspace is needed.  TL2_0 and TL1_0: the lossy table
+ *   Integer-weight layouts (C4G2, C5G2, C3G5): the group codes expanded to int8 and multiplied on int8 MFMA, up to 16
+ *   tokens per slice and all slices in one launch, any M; x_rowsum is not used and no workspace is needed.  TL2_0 and TL1_0: the lossy table
  *   lookups described with the layouts, 8 tokens per launch, any M, no workspace; acc receives their integers.
  *   TL2: one token runs the table lookups of Eq. 3 (tables built in LDS) where the row's tables fit (K <= 14336);
  *   otherwise, up to 16 tokens with 384 <= K < 18816, the packed triples are expanded to int8 weights and
@@ -221,7 +221,7 @@ size_t bitnet_mpgemm_fused_workspace_bytes(int layout, int n_linears, const int6
  *   rewritten in the I2_S layout and one prefill launch, where ws holds all of them) or one bitnet_mpgemm call
  *   per weight.  TL1 runs as I2_S up to 16 tokens (the same launches, the pair codes expanded in registers) and
  *   as TL2 above (every weight rewritten in the I2_S layout, one prefill launch).  The integer-weight layouts run
- *   the quantiser and then the table lookups of each weight.
+ *   the quantiser inside the launch for one token, else the quantiser and one launch for every weight.
  */
 bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* packed, const size_t* packed_bytes,
                                   const float* const* w_scale, const int64_t* N, int64_t K, const float* x,

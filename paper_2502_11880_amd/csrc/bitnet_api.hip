@@ -271,9 +271,9 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
                                         xq, x_scale, M, K, s),
                           "bitnet_mpgemm launch");
     }
-    if (elut_layout(layout))   // table lookups of the integer-weight formats, any M (slices of 2 or 4 tokens)
-        return hip_status(bitnet::launch_elut_generic(elut_format(layout), one_linear(packed, w_scale, N, y, acc), nullptr,
-                                                      xq, x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s),
+    if (elut_layout(layout))   // the integer-weight formats expanded for MFMA, any M (slices of up to 16 tokens)
+        return hip_status(bitnet::launch_elut(elut_format(layout), one_linear(packed, w_scale, N, y, acc), nullptr, xq,
+                                              x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s),
                           "bitnet_mpgemm launch");
     if (i2s_tiled(layout) && (M <= kDecodeMaxTokens || bitnet::i2s_sliced_ok(M, K, x_rowsum != nullptr)))
         return hip_status(bitnet::launch_i2s_decode(one_linear(packed, w_scale, N, y, acc), xq, x_scale, x_rowsum,
@@ -456,14 +456,14 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
                                                             true)
                            : bitnet::launch_tl2_elut_decode(L, x, nullptr, nullptr, 1, (int)K, xq, x_scale, x_rowsum, s,
                                                             true))
-                    : bitnet::launch_elut_generic(elut_format(layout), L, x, nullptr, nullptr, 1, (int)K, xq, x_scale,
+                    : bitnet::launch_elut(elut_format(layout), L, x, nullptr, nullptr, 1, (int)K, xq, x_scale,
                                                   x_rowsum, s);
             return hip_status(e, "bitnet_mpgemm_fused launch");
         }
         hipError_t e = quantise ? bitnet::launch_quantize_act(x, M, K, xq, x_scale, x_rowsum, s) : hipSuccess;
         if (e == hipSuccess)
             e = lossy_layout(layout) ? lookup_sliced(tl1, true, L, xq, x_scale, M, K, s)
-                                     : bitnet::launch_elut_generic(elut_format(layout), L, nullptr, xq, x_scale, (int)M,
+                                     : bitnet::launch_elut(elut_format(layout), L, nullptr, xq, x_scale, (int)M,
                                                                    (int)K, nullptr, nullptr, nullptr, s);
         return hip_status(e, "bitnet_mpgemm_fused launch");
     }

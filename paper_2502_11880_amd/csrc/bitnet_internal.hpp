@@ -166,6 +166,9 @@ hipError_t launch_pack(int layout, const float* W, int64_t N, int64_t K, void* p
 
 constexpr int kMaxSplits = 16;
 int device_cus();
+// Work groups of `threads` threads and `lds` bytes of dynamic LDS of a kernel that are resident on one CU of the current
+// device (at least 1): the runtime's answer, kept in a small table (a query costs about a microsecond of host time).
+int resident_groups(const void* kern, int threads, size_t lds);
 
 // Up to kMaxFused weights that read the same activation, served by one decode launch.
 constexpr int kMaxFused = 8;
@@ -275,16 +278,15 @@ hipError_t launch_tl1_lossy_stream(const FusedLinears& L, const float* x, int K,
 hipError_t launch_tl2_stream(const FusedLinears& L, const float* x, int K, int8_t* xq, float* x_scale,
                              int32_t* x_rowsum, hipStream_t stream, bool lossy = false);
 
-// ELUT for integer weights of other cardinalities: formats c4g2, c5g2 and c3g5 (table lookups, up to 4 tokens per
-// launch for the 2-weight groups and 2 for c3g5; the launcher slices M).  Every weight of L in one launch.  With x
-// (fp32, one token) the launch quantises the row itself and writes xq_out, s_out and rs_out as the quantiser would;
-// otherwise it reads xq and x_scale (M tokens).
+// Integer weights of other cardinalities (formats c4g2, c5g2 and c3g5): the group codes expanded to int8 for MFMA, any
+// M (slices of up to 16 tokens within the launch), every weight of L in one launch.  With x (fp32, one token) the
+// launch quantises the row itself and writes xq_out, s_out and rs_out as the quantiser would; otherwise it reads xq
+// and x_scale (M tokens).
 constexpr int kElutC4G2 = 0;
 constexpr int kElutC5G2 = 1;
 constexpr int kElutC3G5 = 2;
-hipError_t launch_elut_generic(int fmt, const FusedLinears& L, const float* x, const int8_t* xq,
-                               const float* x_scale, int M, int K, int8_t* xq_out, float* s_out, int32_t* rs_out,
-                               hipStream_t stream);
+hipError_t launch_elut(int fmt, const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M,
+                       int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream);
 hipError_t launch_pack_elut(int fmt, const int8_t* Wq, int N, int K, void* packed, hipStream_t stream);
 
 

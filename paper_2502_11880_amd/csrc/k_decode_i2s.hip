@@ -24,6 +24,7 @@
 // multiplies the current one.
 #include "bitnet_internal.hpp"
 
+#include <mutex>
 #include <type_traits>
 
 namespace bitnet {
@@ -597,12 +598,7 @@ hipError_t launch_stream(const FusedLinears& L, const float* x, int K, int8_t* x
     // (to within one).  16-wave groups: one per CU (a second resident group per CU, which the register use of the
     // one-batch start allows, measured slower on the 100B-class stack: 4.96 against 4.74 ms per step); 4-wave
     // groups: as many as fit, every row group in flight at once
-    int occ = 1;
-    if (WAVES < 16 &&
-        (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void*>(kern), 64 * WAVES, lds) !=
-             hipSuccess ||
-         occ <= 0))
-        occ = 1;
+    const int occ = WAVES < 16 ? resident_groups(reinterpret_cast<const void*>(kern), 64 * WAVES, lds) : 1;
     const int total = L.total;
     const int64_t max_g = (int64_t)device_cus() * occ;
     const int64_t rounds = (total + max_g - 1) / max_g;
@@ -644,8 +640,7 @@ hipError_t launch_mstream(const FusedLinears& L, const int8_t* xq, const float* 
     const int per = M < slice ? M : slice;                    // tokens of one slice
     const int slices = (M + per - 1) / per;
     const size_t lds = (size_t)per * (K + 16);
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * W, lds) != hipSuccess || occ <= 0) occ = 1;
+    const int occ = resident_groups(kern, 64 * W, lds);
     int64_t max_g = (int64_t)device_cus() * occ;
     if (slices > 1) max_g = max_g / slices / kNumXcd * kNumXcd;  // every slice resident at once, XCD-aligned columns
     if (max_g < kNumXcd) max_g = kNumXcd;
@@ -685,6 +680,30 @@ int device_cus() {
         cus[dev] = n;
     }
     return cus[dev];
+}
+
+int resident_groups(const void* kern, int threads, size_t lds) {
+    struct Entry {
+        const void* kern;
+        size_t lds;
+        int threads, dev, occ;
+    };
+    constexpr size_t kEntries = 256;                          // direct-mapped: a clash only asks the runtime again
+    static Entry table[kEntries] = {};
+    static std::mutex mu;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    const size_t h = ((reinterpret_cast<uintptr_t>(kern) >> 4) * 31 + lds / 16 * 7 + (size_t)threads + (size_t)dev) % kEntries;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        const Entry& e = table[h];
+        if (e.kern == kern && e.lds == lds && e.threads == threads && e.dev == dev && e.occ > 0) return e.occ;
+    }
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, threads, lds) != hipSuccess || occ <= 0) return 1;
+    std::lock_guard<std::mutex> lock(mu);
+    table[h] = Entry{kern, lds, threads, dev, occ};
+    return occ;
 }
 
 // Waves per work group and blocks per wave per batch.  All waves of a launch should be resident at once

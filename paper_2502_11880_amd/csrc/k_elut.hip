@@ -1,288 +1,489 @@
-// ELUT mpGEMM for integer weights of other cardinalities (Appendix "Insight", Table 3, Algorithm "ELUT mpGEMM",
-// Eq. 3): the weights come from a set of C consecutive integers, every group of g weights is one code, and the
-// accumulation looks the code up in a table of the C^g possible group sums of the token's activations (with mirror
-// consolidation for symmetric sets: the non-negative half of the table, an index and a sign, Eq. 5).
+// Integer-weight ELUT formats (c4g2, c5g2, c3g5; Appendix "Insight", Table 3) on int8 MFMA: the group codes are expanded
+// to int8 weights in registers and multiplied as a dense int8 contraction, which gives the same integer sums as the
+// table lookups of Eq. 3 (the tables hold exactly these products).  One launch serves every weight of a fused group
+// and up to 16 tokens per token slice (blockIdx.y); one token can be quantised inside (QX, Sec. 2.1).
 //
-// Formats (codes as the oracle defines them):
-//   c4g2  C = 4 {-2, -1, 0, 1},  g = 2: 4-bit code = 4 (w0 + 2) + (w1 + 2), 16 entries, 2 bits per weight
-//   c5g2  C = 5 {-2, .., 2},     g = 2: 4-bit index |5 w0 + w1| (13 entries) + a sign plane, 2.5 bits per weight
-//   c3g5  C = 3 {-1, 0, 1},      g = 5: one byte per group, index |sum_j 3^(4-j) w_j| (122 entries) in bits 0-6 and
-//                                       the sign in bit 7, 1.6 bits per weight
-// A 122-entry table does not fit the 16-byte table registers of the paper's CPU kernels (its register-length
-// analysis stops ternary groups at g = 3); in GPU LDS it costs 244 bytes per group and token.
+// Work split.  A work group holds its tokens' codes in LDS for the whole launch and walks the 16-row groups
+// blockIdx.x, blockIdx.x + gridDim.x, ...; its waves split K and meet through LDS once per row group.  The packed rows
+// are row-major, so lane (r, q) of a wave loads the 16 bytes of row r at 64 kb + 16 q of block kb: a block is 64
+// contiguous bytes of 16 rows (256 weights, or 320 for c3g5), and a wave takes U neighbouring blocks so that whole
+// 128-byte lines are used by one wave.  The loads of the next step are in flight while a step is multiplied.
 //
-// Kernel (decode, up to 4 tokens per launch; 2 for c3g5).  A work group of 16 waves owns 16 RS consecutive weight
-// rows (RS per wave) and walks K in blocks of 64 packed words per row: each lane owns word l of a row's block, and
-// the block's tables are built in LDS by the whole group (one entry per thread at a time, from the block's
-// activation codes staged in LDS) before the lanes look their groups up.  Table entry e of group p of token t
-// sits at ((t E' + e) * GB + q) with q = (p mod GW) * 64 + p / GW, so the 64 lanes of a wave reading item i of
-// their words touch 64 consecutive entries when their codes agree.  Each lane keeps one int32 sum per row and
-// token; a wave reduction and the epilogue y = acc * beta / s_t finish each row.  The kernel instance builds the
-// tables of exactly the launch's tokens, and the next block's words and codes are loaded while the current block's
-// tables are built and read.
+// Operands of v_mfma_i32_16x16x64_i8 (B column = weight row r, A row = token, rows past the tokens repeat token 0).
+// Any order of k works as long as both operands agree, so the weights are taken in the order the codes unpack and the
+// activations are put in that order once, when they are copied to LDS:
+//   c4g2, c5g2: 32-bit word j of the lane's 16 bytes holds the weights 16 j + e of its 64; field f of the operand
+//               holds e = 4 b + (f ^ 1) in byte b
+//   c3g5:       byte i of the lane's 16 is the group of weights 5 i + d of its 80; step d takes digit d of all 16
+// Codes are offset to be non-negative (w + 2, or t + 1); the offset times the token's code sum, which the first row
+// group takes from an MFMA against ones, is subtracted in the epilogue.  Codes past K are zero in LDS.
+//
+// What bounds it: at one token the start of a launch and the weight stream, at 8 tokens the same (a lane expands 64
+// weights with 28 VALU operations in c4g2, about 130 in c5g2, about 130 for 80 weights in c3g5).  The 3B-class layer set at
+// 8 tokens, C4G2, 195 -> 46 us per layer
+// (table lookups of 4 tokens per launch before: every work group rebuilt the tables of every block it read); one token
+// 47 -> 28 us, C5G2 57 -> 40 us, C3G5 51 -> 32 us.
 #include "bitnet_internal.hpp"
+
+#include <type_traits>
 
 namespace bitnet {
 namespace {
 
+// The formats: weights of C consecutive integers in groups of G, GW groups to a packed 32-bit word.
+//   c4g2  {-2, -1, 0, 1}: 4-bit code 4 (w0 + 2) + (w1 + 2), 2 bits per weight
+//   c5g2  {-2, .., 2}:    4-bit index |5 w0 + w1| and a sign plane, 2.5 bits per weight
+//   c3g5  {-1, 0, 1}:     one byte per group, index |sum_j 3^(4-j) w_j| (0..121) and the sign in bit 7, 1.6 bits
 template <int F>
 struct ElutFmt;
 template <>
 struct ElutFmt<kElutC4G2> {
-    static constexpr int C = 4, G = 2, E = 16, EP = 16, GW = 8, MT = 4;
+    static constexpr int C = 4, G = 2, GW = 8;
     static constexpr bool kMirror = false;
 };
 template <>
 struct ElutFmt<kElutC5G2> {
-    static constexpr int C = 5, G = 2, E = 13, EP = 16, GW = 8, MT = 4;
+    static constexpr int C = 5, G = 2, GW = 8;
     static constexpr bool kMirror = true;
 };
 template <>
 struct ElutFmt<kElutC3G5> {
-    static constexpr int C = 3, G = 5, E = 122, EP = 128, GW = 4, MT = 2;
+    static constexpr int C = 3, G = 5, GW = 4;
     static constexpr bool kMirror = true;
 };
 
-constexpr int kEW = 16;                  // waves per work group
-constexpr int kEThreads = 64 * kEW;
+typedef unsigned short us2 __attribute__((ext_vector_type(2)));
 
-// Weight j of every table entry e, as a compile-time table: the base-C digits of e offset by the set's minimum, or
-// with mirroring the balanced base-C digits of e; weight 0 is the most significant digit.  A table entry is then a
-// sum of the group's codes with constant coefficients.
 template <int F>
-struct DigitTable {
-    int8_t d[ElutFmt<F>::E][ElutFmt<F>::G];
-    constexpr DigitTable() : d{} {
-        using T = ElutFmt<F>;
-        for (int e = 0; e < T::E; ++e) {
-            int v = e;
-            for (int j = T::G - 1; j >= 0; --j) {
-                int r = 0;
-                if (T::kMirror) {
-                    r = v % T::C;
-                    if (r > T::C / 2) r -= T::C;
-                    v = (v - r) / T::C;
-                } else {
-                    r = v % T::C - T::C / 2;
-                    v /= T::C;
-                }
-                d[e][j] = (int8_t)r;
-            }
-        }
-    }
+struct MfmaFmt {                                    // c4g2, c5g2
+    static constexpr int BK = 256, OFF = 2;
+    static constexpr int row_div = 4;               // weights per packed byte
+};
+template <>
+struct MfmaFmt<kElutC3G5> {
+    static constexpr int BK = 320, OFF = 1;
+    static constexpr int row_div = 5;
 };
 
-// One launch serves every weight of a fused group (rows concatenated, each row's weight found by a scalar compare
-// chain), since the tables depend only on the activation.  QX (one token): the work group quantises the fp32 row
-// itself (Sec. 2.1): the row's absmax first (a pass over the row, L2-resident after the first work groups), then
-// every block's codes from its fp32 values as the block is staged; work group 0 writes the codes, the scale and
-// their sum, as the quantiser would.
-template <int F, int RS, int MT, bool QX>
-__global__ __launch_bounds__(kEThreads) void elut_generic_kernel(FusedLinears L, const float* __restrict__ x,
-                                                                 const int8_t* __restrict__ xq,
-                                                                 const float* __restrict__ x_scale, int M, int K,
-                                                                 int8_t* __restrict__ xq_out, float* __restrict__ s_out,
-                                                                 int32_t* __restrict__ rs_out) {
-    using T = ElutFmt<F>;
-    constexpr int GB = 64 * T::GW;                // groups per block
-    constexpr int KB = GB * T::G;                 // weights per block
-    constexpr int kTab = MT * T::EP * GB;         // int16 entries
-    constexpr int kXw = MT * (KB / 4);            // 32-bit words of activation codes per block
-    static_assert(kXw <= kEThreads, "one word of codes per thread and block");
-    static_assert(!QX || MT == 1, "the fused quantiser takes one token");
-    __shared__ int16_t tab[kTab];
-    __shared__ __align__(16) int8_t xs[MT][KB];
-    __shared__ float redf[kEW];
-    __shared__ int redi[kEW];
-    constexpr DigitTable<F> kDig{};
+// Offset codes (w + 2) of the 16 weights of a c5g2 word: indices |5 w0 + w1| of 8 groups in nibbles, their signs in the
+// low 8 bits of sg.  Byte arithmetic on four groups at a time; no byte over- or underflows.
+__device__ __forceinline__ v4i c5_codes(uint32_t w, uint32_t sg) {
+    v4i b;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t idx2 = ((w >> (4 * h)) & 0x0F0F0F0Fu) + 0x02020202u;        // |5 w0 + w1| + 2: 2..14
+        // w0 of the positive group: (index + 2) / 5 = 13 (index + 2) / 64 for these; then w1 + 2 in 0..4
+        const uint32_t a0 = ((idx2 * 13u) >> 6) & 0x03030303u;
+        const uint32_t c1 = idx2 - 5u * a0;
+        // sign bit 2 b + h of group 2 b + h to bit 8 b (masked first: the shifted copies never carry into one)
+        const uint32_t m = (((sg >> h) & 0x55u) * 0x00041041u) & 0x01010101u;
+        const uint32_t m3 = m * 3u;
+        // negative groups: w0 + 2 = 2 - a0, w1 + 2 = 4 - c1
+        const uint32_t w0 = (a0 ^ m3) + 0x02020202u - m3;                          // 3 - a0 - 1
+        const uint32_t w1 = (c1 ^ (m * 7u)) - m3;                                  // 7 - c1 - 3
+        if (h == 0) {
+            b.x = (int)w1;
+            b.y = (int)w0;
+        } else {
+            b.z = (int)w1;
+            b.w = (int)w0;
+        }
+    }
+    return b;
+}
+
+// The digits t + 1 of four c3g5 groups (one byte each), most significant first: d[j] holds digit j of the four.
+__device__ __forceinline__ void c3_digits(uint32_t g, uint32_t (&d)[5]) {
+    const uint32_t s = (g >> 7) & 0x01010101u, s7 = (s << 7) - s;
+    // 121 + value: 121 + index, or 127 - index + 121 - 127 where the sign is set; 0..242
+    const uint32_t u = ((g & 0x7F7F7F7Fu) ^ s7) + 0x79797979u - s7;
+    us2 e = __builtin_bit_cast(us2, u & 0x00FF00FFu), o = __builtin_bit_cast(us2, (u >> 8) & 0x00FF00FFu);
+#pragma unroll
+    for (int j = 4; j >= 1; --j) {
+        const us2 qe = (e * (unsigned short)171) >> (unsigned short)9;             // x / 3 for x < 256
+        const us2 qo = (o * (unsigned short)171) >> (unsigned short)9;
+        const us2 de = e - qe * (unsigned short)3, dd = o - qo * (unsigned short)3;
+        d[j] = __builtin_bit_cast(uint32_t, de) | (__builtin_bit_cast(uint32_t, dd) << 8);
+        e = qe;
+        o = qo;
+    }
+    d[0] = __builtin_bit_cast(uint32_t, e) | (__builtin_bit_cast(uint32_t, o) << 8);
+}
+
+// 16 codes in the order of the c4g2 and c5g2 operands: byte b of word f is code 4 b + (f ^ 1).
+__device__ __forceinline__ v4i order_pairs(v4i a) {
+    // v_perm_b32(hi, lo): bytes 0..3 of the selector's numbering are lo, 4..7 hi
+    const uint32_t e01 = __builtin_amdgcn_perm((uint32_t)a.y, (uint32_t)a.x, 0x06020400u);  // x0 y0 x2 y2
+    const uint32_t o01 = __builtin_amdgcn_perm((uint32_t)a.y, (uint32_t)a.x, 0x07030501u);  // x1 y1 x3 y3
+    const uint32_t e23 = __builtin_amdgcn_perm((uint32_t)a.w, (uint32_t)a.z, 0x06020400u);
+    const uint32_t o23 = __builtin_amdgcn_perm((uint32_t)a.w, (uint32_t)a.z, 0x07030501u);
+    v4i o;
+    o.x = (int)__builtin_amdgcn_perm(o23, o01, 0x05040100u);                                // x1 y1 z1 w1
+    o.y = (int)__builtin_amdgcn_perm(e23, e01, 0x05040100u);                                // x0 y0 z0 w0
+    o.z = (int)__builtin_amdgcn_perm(o23, o01, 0x07060302u);                                // x3 y3 z3 w3
+    o.w = (int)__builtin_amdgcn_perm(e23, e01, 0x07060302u);                                // x2 y2 z2 w2
+    return o;
+}
+
+// Where code k of a token goes in its LDS row.
+template <int F>
+__device__ __forceinline__ int code_pos(int k) {
+    if constexpr (F == kElutC3G5) {
+        const int u = k / 80, e = k - 80 * u, i = e / 5, d = e - 5 * i;
+        return 80 * u + 16 * d + i;
+    } else {
+        return (k & ~15) + 4 * ((k & 3) ^ 1) + ((k >> 2) & 3);
+    }
+}
+
+template <int F, int WAVES, int U, bool QX>
+__global__ __launch_bounds__(64 * WAVES) void elut_kernel(FusedLinears L, const float* __restrict__ x,
+                                                               const int8_t* __restrict__ xq,
+                                                               const float* __restrict__ x_scale, int M, int K,
+                                                               int slice, int8_t* __restrict__ xq_out,
+                                                               float* __restrict__ s_out, int32_t* __restrict__ rs_out) {
+    using T = MfmaFmt<F>;
+    constexpr int kThreads = 64 * WAVES;
+    extern __shared__ __align__(16) int8_t xs[];    // token rows of nkb BK codes + 16 bytes
+    __shared__ v4i part[2][WAVES][64];
+    __shared__ int rs_s[WAVES][16];
+    __shared__ float redf[WAVES];
+
+    const int m0 = (int)blockIdx.y * slice;         // this work group's token slice
+    M = min(M - m0, slice);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int Gtot = K / T::G;                    // groups per row
-    const int nblk = (Gtot + GB - 1) / GB;
-    const int rows = L.total * kRowsPerGroup;     // rows of all the launch's weights
-    const int row0 = blockIdx.x * (kEW * RS) + wave * RS;
-    const size_t row_bytes = T::GW == 8 ? (size_t)K / 4 : (size_t)K / 5;   // index plane (c4g2, c5g2) or bytes
+    const int q = lane >> 4, r = lane & 15;
+    const int G = gridDim.x, bid = blockIdx.x;
+    const int nkb = (K + T::BK - 1) / T::BK;
+    const int stride = nkb * T::BK + 16;            // an odd multiple of 16: the rows of an operand read in other banks
+    const int nb = (nkb + WAVES * U - 1) / (WAVES * U);
+    const int S = ((L.total - bid + G - 1) / G) * nb;
+    const uint32_t row_bytes = (uint32_t)K / T::row_div;
 
-    // this wave's rows: weight, row within it, packed row and (c5g2) sign row; rows past the last are clamped
-    // to it and never stored
-    int rli[RS], rn[RS];
-    const uint8_t* rpk[RS];
-    const uint8_t* rsg[RS];
-#pragma unroll
-    for (int r = 0; r < RS; ++r) {
-        const int nc = min(row0 + r, rows - 1);
-        int li, rg;
-        locate(L, nc / kRowsPerGroup, li, rg);
-        rli[r] = li;
-        rn[r] = rg * kRowsPerGroup + nc % kRowsPerGroup;
+    // step st = batch st % nb of row group bid + (st / nb) G
+    auto step_gb = [&](int st, int& g, int& b) {
+        const int gi = nb == 1 ? st : st / nb;
+        b = st - gi * nb;
+        g = bid + gi * G;
+    };
+    struct Batch {
+        v4u w[U];
+        uint32_t sg[F == kElutC5G2 ? U : 1];
+        float bw;
+    };
+    auto issue = [&](Batch& B, int st) {
+        int g, b, li, rg;
+        step_gb(st, g, b);
+        locate(L, g, li, rg);
         const uint8_t* base = pick(L.packed, li);
-        rpk[r] = base + (size_t)rn[r] * row_bytes;
-        rsg[r] = base + (size_t)pick(L.N, li) * K / 4 + (size_t)rn[r] * (K / 16);   // c5g2 only
-    }
-
-    // QX: the row's scale (the quantiser's formula) before the first block
-    float sx = 1.0f;
-    int csum = 0;                                 // QX, work group 0: this thread's share of the code sum
-    if constexpr (QX) {
-        const float4* x4 = reinterpret_cast<const float4*>(x);
-        float amax = 0.0f;
-        for (int i = tid; i < K / 4; i += kEThreads) {
-            const float4 v = x4[i];
-            amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+        const uint32_t n = (uint32_t)(rg * kRowsPerGroup + r);
+        const int kb0 = b * (WAVES * U) + wave * U;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            // chunks past the row read its last one (their activation codes are zero, or the block is not multiplied)
+            const uint32_t off = min((uint32_t)(64 * (kb0 + u) + 16 * q), row_bytes - 16u);
+            B.w[u] = load_stream16(base + ((size_t)n * row_bytes + off));
+            if constexpr (F == kElutC5G2)
+                B.sg[u] = *reinterpret_cast<const uint32_t*>(base + (size_t)pick(L.N, li) * row_bytes +
+                                                             ((size_t)n * (row_bytes / 4) + off / 4));
         }
+        B.bw = *pick(L.w_scale, li);
+    };
+
+    Batch A0, A1;
+    float sx = 1.0f;
+    const v4i zero = {0, 0, 0, 0};
+    if constexpr (QX) {
+        // the row in registers (up to kXV float4 per thread, longer rows read twice), its absmax, its codes
+        constexpr int kXV = 4;
+        const float4* x4 = reinterpret_cast<const float4*>(x);
+        const int K4 = K >> 2;
+        float4 xv[kXV];
+        float amax = 0.0f;
+        auto amax4 = [&](const float4& v) {
+            amax = fmaxf(amax, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+        };
+#pragma unroll
+        for (int i = 0; i < kXV; ++i) xv[i] = x4[min(tid + i * kThreads, K4 - 1)];
+        __builtin_amdgcn_s_barrier();               // every wave's row loads before any weight load
+        issue(A0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < kXV; ++i) amax4(xv[i]);  // a repeated element changes nothing
+        for (int e = tid + kXV * kThreads; e < K4; e += kThreads) amax4(x4[e]);
         amax = wave_max_all(amax);
         if (lane == 0) redf[wave] = amax;
         __syncthreads();
         amax = redf[0];
 #pragma unroll
-        for (int w = 1; w < kEW; ++w) amax = fmaxf(amax, redf[w]);
+        for (int w = 1; w < WAVES; ++w) amax = fmaxf(amax, redf[w]);
         sx = 127.0f / fmaxf(amax, 1e-5f);
-    }
-
-    // The loads of block kb: this wave's packed words (lane l: word l of each of its rows) and one word of the
-    // block's activation codes per thread (token tid / (KB/4)), or with QX the float4 it quantises.  Addresses are
-    // clamped to real words and the values past the block, the rows or the tokens zeroed, so every load is
-    // unconditional.
-    auto load_block = [&](int kb, uint32_t (&wv)[RS], uint32_t (&sv)[RS], uint32_t& xv, float4& xf) {
-        const int gin = min(GB, Gtot - kb * GB);
-        const int words = (gin + T::GW - 1) / T::GW;
-        const int kin = gin * T::G;
-        const int l = min(lane, words - 1);
+        auto put = [&](const float4& v, int e) {
+            const uint32_t c = quant4(v, sx);
 #pragma unroll
-        for (int r = 0; r < RS; ++r) {
-            const bool ok = row0 + r < rows && lane < words;
-            const uint32_t w = *reinterpret_cast<const uint32_t*>(rpk[r] + (size_t)kb * 256 + 4 * l);
-            wv[r] = ok ? w : 0u;
-            if constexpr (F == kElutC5G2) {
-                const uint32_t sg = rsg[r][(size_t)kb * 64 + l];
-                sv[r] = ok ? sg : 0u;
-            } else {
-                sv[r] = 0u;
+            for (int p = 0; p < 4; ++p) xs[code_pos<F>(4 * e + p)] = (int8_t)(c >> (8 * p));
+            if (bid == 0) reinterpret_cast<uint32_t*>(xq_out)[e] = c;
+        };
+#pragma unroll
+        for (int i = 0; i < kXV; ++i)
+            if (tid + i * kThreads < K4) put(xv[i], tid + i * kThreads);
+        for (int e = tid + kXV * kThreads; e < K4; e += kThreads) put(x4[e], e);
+        for (int k = K + 16 * tid; k < nkb * T::BK; k += 16 * kThreads) *reinterpret_cast<v4i*>(xs + k) = zero;
+        if (bid == 0 && tid == 0) s_out[0] = sx;
+    } else {
+        // Each wave copies the codes of its own blocks, every token, in the operands' order; no other wave reads them.
+        // The first eight tokens' loads of the first batch go out before any weight load, and the barrier keeps the
+        // last waves' codes from queueing behind the first waves' weights.
+        const int8_t* src = xq + (size_t)m0 * K;
+        auto start = [&]() {
+            __builtin_amdgcn_s_barrier();
+            issue(A0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        if constexpr (F == kElutC3G5) {
+            // lane: token lane / 4, run lane % 4 (80 codes) of a block; every load in bounds, stores where it is real
+            const int m = lane >> 2;
+            for (int b = 0; b < nb; ++b) {
+                for (int u = 0; u < U; ++u) {
+                    const int k = (b * (WAVES * U) + wave * U + u) * T::BK + 80 * (lane & 3);
+                    const int8_t* p = src + (size_t)min(m, M - 1) * K + min(k, K - 80);
+                    uint32_t in[20];
+#pragma unroll
+                    for (int i = 0; i < 5; ++i) {
+                        const v4u v = *reinterpret_cast<const v4u*>(p + 16 * i);
+                        in[4 * i] = v.x;
+                        in[4 * i + 1] = v.y;
+                        in[4 * i + 2] = v.z;
+                        in[4 * i + 3] = v.w;
+                    }
+                    if (b == 0 && u == 0) start();
+                    if (m < M && k < K) {
+#pragma unroll
+                        for (int d = 0; d < 5; ++d) {
+                            v4u o;
+#pragma unroll
+                            for (int f = 0; f < 4; ++f) {
+                                uint32_t word = 0u;
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const int kk = 5 * (4 * f + e) + d;
+                                    word |= ((in[kk >> 2] >> (8 * (kk & 3))) & 0xFFu) << (8 * e);
+                                }
+                                o[f] = word;
+                            }
+                            *reinterpret_cast<v4u*>(xs + m * stride + k + 16 * d) = o;
+                        }
+                    }
+                }
+            }
+        } else {
+            // lane: token lane / 16 of four, 16-byte chunk lane % 16 of a block; eight tokens at a time
+            const int end = nkb * T::BK;
+            for (int b = 0; b < nb; ++b) {
+                const int kw = (b * (WAVES * U) + wave * U) * T::BK + 16 * r;
+                for (int mg = 0; mg < M; mg += 8) {
+                    v4i in[2][U];
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            in[h][u] = *reinterpret_cast<const v4i*>(src + (size_t)min(mg + 4 * h + q, M - 1) * K +
+                                                                     min(kw + u * T::BK, K - 16));
+                    if (b == 0 && mg == 0) start();
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int m = mg + 4 * h + q, k = kw + u * T::BK;
+                            if (m < M && k < end)
+                                *reinterpret_cast<v4i*>(xs + m * stride + k) = k < K ? order_pairs(in[h][u]) : zero;
+                        }
+                }
             }
         }
-        const int t = tid / (KB / 4), w = tid - t * (KB / 4);
-        const bool xok = tid < kXw && t < M && 4 * w < kin;
-        const size_t off = (size_t)kb * KB + min(4 * w, kin - 4);
-        if constexpr (QX) {
-            const float4 v = *reinterpret_cast<const float4*>(x + off);
-            xf = xok ? v : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            xv = 0u;
-        } else {
-            const uint32_t v = *reinterpret_cast<const uint32_t*>(xq + (size_t)min(t, M - 1) * K + off);
-            xv = xok ? v : 0u;
+        wave_lds_handoff();
+    }
+    // epilogue operands of tokens m = 4 q + v
+    float xs_m[4];
+    int off_m[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) xs_m[v] = QX ? sx : x_scale[m0 + min(4 * q + v, M - 1)];
+
+    v4i acc = zero, rsum = zero;
+    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+    const int8_t* arow = xs + (r < M ? r : 0) * stride + q * (T::BK / 4);
+    int par = 0;
+    // FIRST: the work group's first row group, which also sums the codes
+    auto compute = [&](const Batch& B, int st, auto first) {
+        constexpr bool kFirst = decltype(first)::value;
+        int g, b;
+        step_gb(st, g, b);
+        if (b == 0) acc = zero;
+        const int kb0 = b * (WAVES * U) + wave * U;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (kb0 + u < nkb) {
+                const int8_t* ab = arow + (kb0 + u) * T::BK;
+                if constexpr (F == kElutC3G5) {
+                    uint32_t d0[5], d1[5], d2[5], d3[5];
+                    c3_digits(B.w[u].x, d0);
+                    c3_digits(B.w[u].y, d1);
+                    c3_digits(B.w[u].z, d2);
+                    c3_digits(B.w[u].w, d3);
+#pragma unroll
+                    for (int j = 0; j < 5; ++j) {
+                        const v4i a = *reinterpret_cast<const v4i*>(ab + 16 * j);
+                        acc = mfma16x16x64(a, v4i{(int)d0[j], (int)d1[j], (int)d2[j], (int)d3[j]}, acc);
+                        if constexpr (kFirst) rsum = mfma16x16x64(a, ones, rsum);
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const v4i a = *reinterpret_cast<const v4i*>(ab + 16 * j);
+                        const uint32_t w = word_of(B.w[u], j);
+                        const v4i c = F == kElutC5G2 ? c5_codes(w, (B.sg[F == kElutC5G2 ? u : 0] >> (8 * j)) & 0xFFu)
+                                                     : unpack_codes(w);
+                        acc = mfma16x16x64(a, c, acc);
+                        if constexpr (kFirst) rsum = mfma16x16x64(a, ones, rsum);
+                    }
+                }
+            }
         }
+        if (b != nb - 1) return;
+        part[par][wave][lane] = acc;
+        if constexpr (kFirst) {
+            if (r == 0) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) rs_s[wave][4 * q + v] = rsum[v];
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            if constexpr (kFirst) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    int t = 0;
+#pragma unroll
+                    for (int w2 = 0; w2 < WAVES; ++w2) t += rs_s[w2][4 * q + v];
+                    off_m[v] = T::OFF * t;
+                    if (QX && v == 0 && bid == 0 && tid == 0) rs_out[0] = t;
+                }
+            }
+            if (4 * q < M) {
+                v4i tot = part[par][0][lane];
+#pragma unroll 4
+                for (int w2 = 1; w2 < WAVES; ++w2) tot += part[par][w2][lane];
+                int li, rg;
+                locate(L, g, li, rg);
+                const int N = pick(L.N, li);
+                const int n = rg * kRowsPerGroup + r;
+                float* y = pick(L.y, li);
+                int32_t* acc_out = pick(L.acc, li);
+                // D element v of lane l is row 4 (l / 16) + v (token), column l % 16 (weight row)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int m = 4 * q + v;
+                    if (m < M) {
+                        const int val = tot[v] - off_m[v];
+                        y[(size_t)(m0 + m) * N + n] = (float)val * (B.bw / xs_m[v]);
+                        if (acc_out) acc_out[(size_t)(m0 + m) * N + n] = val;
+                    }
+                }
+            }
+        }
+        par ^= 1;
     };
 
-    int acc[RS][MT];
-#pragma unroll
-    for (int r = 0; r < RS; ++r)
-#pragma unroll
-        for (int t = 0; t < MT; ++t) acc[r][t] = 0;
+    const std::true_type kFirstGroup{};
+    const std::false_type kLaterGroup{};
+    if (S == 1) {
+        if constexpr (QX) __syncthreads();          // the codes are in LDS
+        compute(A0, 0, kFirstGroup);
+        return;
+    }
+    issue(A1, 1);
+    if constexpr (QX) __syncthreads();
+    // steps st and st + 1 are in flight; each set is refilled right after it is multiplied (past the last step: the
+    // last one again, never multiplied)
+    auto step = [&](Batch& B, int st) {
+        if (st < nb) compute(B, st, kFirstGroup);
+        else compute(B, st, kLaterGroup);
+        issue(B, min(st + 2, S - 1));
+    };
+    int st = 0;
+    for (; st + 1 < S; st += 2) {
+        step(A0, st);
+        step(A1, st + 1);
+    }
+    if (st < S) step(A0, st);
+}
 
-    // Block kb + 1's loads are issued before block kb's tables are built, so they land during its arithmetic.
-    uint32_t wn[RS], sn[RS], xn;
-    float4 xfn;
-    load_block(0, wn, sn, xn, xfn);
-    for (int kb = 0; kb < nblk; ++kb) {
-        uint32_t wv[RS], sv[RS];
-#pragma unroll
-        for (int r = 0; r < RS; ++r) {
-            wv[r] = wn[r];
-            sv[r] = sn[r];
+constexpr size_t kElutLds = 120 * 1024;             // dynamic LDS of a launch (16 waves hold 34 KiB beside it)
+
+template <int F, int WAVES, int U>
+hipError_t launch_cfg(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M, int K,
+                      int slice, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
+    using T = MfmaFmt<F>;
+    const int nkb = (K + T::BK - 1) / T::BK;
+    const int per = M < slice ? M : slice;
+    const size_t lds = (size_t)per * (size_t)(nkb * T::BK + 16);
+    const void* kern = x ? reinterpret_cast<const void*>(elut_kernel<F, WAVES, U, true>)
+                         : reinterpret_cast<const void*>(elut_kernel<F, WAVES, U, false>);
+    const int occ = resident_groups(kern, 64 * WAVES, lds);
+    constexpr int kMaxSlices = 4096;                // of one launch (grid y)
+    for (int s0 = 0; s0 * (int64_t)per < M; s0 += kMaxSlices) {
+        const int m0 = s0 * per;
+        const int mc = (int64_t)(M - m0) < (int64_t)kMaxSlices * per ? M - m0 : kMaxSlices * per;
+        const int slices = (mc + per - 1) / per;
+        // as many work groups as are resident at once, balanced over the row groups; with token slices the columns
+        // are a multiple of 8, so that the slices of a row group run on one XCD and share its weight bytes in L2
+        int64_t max_g = (int64_t)device_cus() * occ;
+        if (slices > 1) max_g = max_g / slices / kNumXcd * kNumXcd;
+        if (max_g < kNumXcd) max_g = kNumXcd;
+        const int64_t rounds = (L.total + max_g - 1) / max_g;
+        int64_t gx = (L.total + rounds - 1) / rounds;
+        if (slices > 1 && gx > kNumXcd) gx = gx / kNumXcd * kNumXcd;
+        FusedLinears Ls = L;
+        for (int i = 0; i < L.count; ++i) {
+            Ls.y[i] = L.y[i] + (size_t)m0 * L.N[i];
+            Ls.acc[i] = L.acc[i] ? L.acc[i] + (size_t)m0 * L.N[i] : nullptr;
         }
-        uint32_t xv = xn;
-        if constexpr (QX) {
-            // the block's codes from its fp32 values (zeros past the block quantise to zero codes)
-            xv = quant4(xfn, sx);
-            if (blockIdx.x == 0 && tid < kXw) {
-                const int kin = min(GB, Gtot - kb * GB) * T::G;
-                if (4 * tid < kin) {
-                    reinterpret_cast<uint32_t*>(xq_out + (size_t)kb * KB)[tid] = xv;
-                    csum = byte_sum4(xv, csum);
-                }
-            }
-        }
-        const int gin = min(GB, Gtot - kb * GB);             // groups in this block
-        const int words = (gin + T::GW - 1) / T::GW;         // packed words per row in this block
-        // 1. the block's activation codes into LDS (after every wave is done with the previous block's tables)
-        __syncthreads();
-        if (tid < kXw) reinterpret_cast<uint32_t*>(&xs[0][0])[tid] = xv;
-        load_block(min(kb + 1, nblk - 1), wn, sn, xn, xfn);
-        __syncthreads();
-        // 2. the tables: one thread per token and group reads the group's codes once and writes all its entries,
-        //    entry e = sum_j d_j(e) a_j with the digits as constants (groups past the block give zeros)
-        for (int i = tid; i < MT * GB; i += kEThreads) {
-            const int q = i % GB, t = i / GB;
-            const int p = (q % 64) * T::GW + q / 64;
-            int a[T::G];
-#pragma unroll
-            for (int j = 0; j < T::G; ++j) a[j] = p < gin ? (int)xs[t][p * T::G + j] : 0;
-            int16_t* col = tab + (size_t)t * T::EP * GB + q;
-#pragma unroll
-            for (int e = 0; e < T::E; ++e) {
-                int v = 0;
-#pragma unroll
-                for (int j = 0; j < T::G; ++j) v += (int)kDig.d[e][j] * a[j];
-                col[e * GB] = (int16_t)v;
-            }
-        }
-        __syncthreads();
-        // 3. lookups: item i of lane l's word is group l GW + i, at table column i 64 + l
-        if (lane < words) {
-#pragma unroll
-            for (int r = 0; r < RS; ++r) {
-#pragma unroll
-                for (int i = 0; i < T::GW; ++i) {
-                    int idx, m;
-                    if constexpr (F == kElutC3G5) {
-                        const uint32_t b = (wv[r] >> (8 * i)) & 0xFFu;
-                        idx = (int)(b & 0x7Fu);
-                        m = -(int)(b >> 7);
-                    } else {
-                        idx = (int)((wv[r] >> (4 * i)) & 0xFu);
-                        m = F == kElutC5G2 ? -(int)((sv[r] >> i) & 1u) : 0;
-                    }
-                    const int col = i * 64 + lane;
-#pragma unroll
-                    for (int t = 0; t < MT; ++t) {
-                        const int v = tab[(t * T::EP + idx) * GB + col];
-                        acc[r][t] += (v + m) ^ m;            // Eq. 5: the sign bit widened to a mask
-                    }
-                }
-            }
-        }
+        const dim3 grid((unsigned)gx, (unsigned)slices), block(64 * WAVES);
+        if (x)
+            hipLaunchKernelGGL((elut_kernel<F, WAVES, U, true>), grid, block, lds, stream, Ls, x, xq, x_scale, mc, K,
+                               per, xq_out, s_out, rs_out);
+        else
+            hipLaunchKernelGGL((elut_kernel<F, WAVES, U, false>), grid, block, lds, stream, Ls, x,
+                               xq + (size_t)m0 * K, x_scale + m0, mc, K, per, xq_out, s_out, rs_out);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
     }
-    // 4. every row's sum over the lanes, then the epilogue
-#pragma unroll
-    for (int r = 0; r < RS; ++r) {
-        const int li = rli[r], n = rn[r], N = pick(L.N, li);
-        const float beta = *pick(L.w_scale, li);
-        float* y = pick(L.y, li);
-        int32_t* acc_out = pick(L.acc, li);
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-            const int total = wave_sum_all(acc[r][t]);
-            if (lane == 0 && row0 + r < rows && t < M) {
-                y[(size_t)t * N + n] = (float)total * (beta / (QX ? sx : x_scale[t]));
-                if (acc_out) acc_out[(size_t)t * N + n] = total;
-            }
-        }
+    return hipSuccess;
+}
+
+template <int F>
+hipError_t launch_fmt(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M, int K,
+                      int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t s) {
+    using T = MfmaFmt<F>;
+    const int nkb = (K + T::BK - 1) / T::BK;
+    const int64_t fit = (int64_t)(kElutLds / (size_t)(nkb * T::BK + 16));
+    const int slice = fit < 16 ? (int)fit : 16;
+    // 4-wave groups where a row fits one batch of theirs and there are row groups for half the CUs: several groups per
+    // CU do not wait on one another's barriers.  Otherwise 16 waves, the batches of a row group balanced (up to two
+    // blocks per wave: with more the kernel spills).  Rows of K > 122000 leave LDS only for the partial sums of 8 waves.
+    if (nkb <= 16 && L.total > device_cus() / 2) {
+        const int u = (nkb + 3) / 4;
+        if (u <= 1) return launch_cfg<F, 4, 1>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
+        if (u <= 2) return launch_cfg<F, 4, 2>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
+        if (u <= 3) return launch_cfg<F, 4, 3>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
+        return launch_cfg<F, 4, 4>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
     }
-    if constexpr (QX) {
-        if (blockIdx.x == 0) {
-            csum = wave_sum_all(csum);
-            if (lane == 0) redi[wave] = csum;
-            __syncthreads();
-            if (tid == 0) {
-                int tot = 0;
-#pragma unroll
-                for (int w = 0; w < kEW; ++w) tot += redi[w];
-                rs_out[0] = tot;
-                s_out[0] = sx;
-            }
-        }
-    }
+    if (fit < 1) return launch_cfg<F, 8, 2>(L, x, xq, x_scale, M, K, 1, xq_out, s_out, rs_out, s);
+    const int nb = (nkb + 31) / 32, u = (nkb + 16 * nb - 1) / (16 * nb);
+    if (u <= 1) return launch_cfg<F, 16, 1>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
+    return launch_cfg<F, 16, 2>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
 }
 
 // Packing: one thread per packed word of a row (c4g2 and c5g2: 8 groups, plus their sign byte; c3g5: 4 groups).
@@ -316,64 +517,6 @@ __global__ __launch_bounds__(256) void pack_elut_words(const int8_t* __restrict_
     if constexpr (F == kElutC5G2) packed[(size_t)N * K / 4 + n * (K / 16) + w] = (uint8_t)sign;
 }
 
-template <int F, int RS, int MT, bool QX>
-hipError_t launch_elut_mt(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M, int K,
-                          int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
-    const int64_t rows = (int64_t)L.total * kRowsPerGroup;
-    const dim3 grid((unsigned)((rows + kEW * RS - 1) / (kEW * RS))), block(kEThreads);
-    hipLaunchKernelGGL((elut_generic_kernel<F, RS, MT, QX>), grid, block, 0, stream, L, x, xq, x_scale, M, K, xq_out,
-                       s_out, rs_out);
-    return hipGetLastError();
-}
-
-// Tokens in slices of up to T::MT per launch; the kernel instance builds tables for exactly the slice's tokens
-// (1, 2 or 4).  With x given (one token) the launch quantises the row itself.
-template <int F, int RS>
-hipError_t launch_elut_rs(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M,
-                          int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
-    using T = ElutFmt<F>;
-    if (x) return launch_elut_mt<F, RS, 1, true>(L, x, nullptr, nullptr, 1, K, xq_out, s_out, rs_out, stream);
-    for (int m0 = 0; m0 < M; m0 += T::MT) {
-        const int mc = M - m0 < T::MT ? M - m0 : T::MT;
-        FusedLinears Ls = L;
-        for (int i = 0; i < L.count; ++i) {
-            Ls.y[i] = L.y[i] + (size_t)m0 * L.N[i];
-            Ls.acc[i] = L.acc[i] ? L.acc[i] + (size_t)m0 * L.N[i] : nullptr;
-        }
-        const int8_t* xs = xq + (size_t)m0 * K;
-        hipError_t e;
-        if (mc == 1) e = launch_elut_mt<F, RS, 1, false>(Ls, nullptr, xs, x_scale + m0, mc, K, nullptr, nullptr, nullptr, stream);
-        else if (mc == 2 || T::MT < 4)
-            e = launch_elut_mt<F, RS, 2, false>(Ls, nullptr, xs, x_scale + m0, mc, K, nullptr, nullptr, nullptr, stream);
-        else
-            e = launch_elut_mt<F, RS, (T::MT >= 4 ? 4 : 2), false>(Ls, nullptr, xs, x_scale + m0, mc, K, nullptr, nullptr,
-                                                                   nullptr, stream);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <int F>
-hipError_t launch_elut_fmt(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M, int K,
-                           int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
-    // rows per wave: the fewest that keep the launch within one work group per CU (up to 8 rows per wave), so the
-    // grid uses as many CUs as the rows allow (rounding up to a power of two left up to half of them idle: the
-    // 3B-class layer set at one token, C4G2 54.7 -> 48.2 us per step with 3 and 6 rows allowed)
-    const int cus = device_cus();
-    const int64_t rows = (int64_t)L.total * kRowsPerGroup;
-    const int64_t rs_need = (rows + kEW * cus - 1) / (kEW * cus);
-    switch (rs_need <= 1 ? 1 : rs_need >= 8 ? 8 : (int)rs_need) {
-        case 1: return launch_elut_rs<F, 1>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 2: return launch_elut_rs<F, 2>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 3: return launch_elut_rs<F, 3>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 4: return launch_elut_rs<F, 4>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 5: return launch_elut_rs<F, 5>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 6: return launch_elut_rs<F, 6>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case 7: return launch_elut_rs<F, 7>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        default: return launch_elut_rs<F, 8>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-    }
-}
-
 template <int F>
 hipError_t launch_pack_fmt(const int8_t* Wq, int N, int K, void* packed, hipStream_t stream) {
     using T = ElutFmt<F>;
@@ -385,13 +528,12 @@ hipError_t launch_pack_fmt(const int8_t* Wq, int N, int K, void* packed, hipStre
 
 }  // namespace
 
-hipError_t launch_elut_generic(int fmt, const FusedLinears& L, const float* x, const int8_t* xq,
-                               const float* x_scale, int M, int K, int8_t* xq_out, float* s_out, int32_t* rs_out,
-                               hipStream_t stream) {
+hipError_t launch_elut(int fmt, const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M,
+                            int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
     switch (fmt) {
-        case kElutC4G2: return launch_elut_fmt<kElutC4G2>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        case kElutC5G2: return launch_elut_fmt<kElutC5G2>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
-        default: return launch_elut_fmt<kElutC3G5>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
+        case kElutC4G2: return launch_fmt<kElutC4G2>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
+        case kElutC5G2: return launch_fmt<kElutC5G2>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
+        default: return launch_fmt<kElutC3G5>(L, x, xq, x_scale, M, K, xq_out, s_out, rs_out, stream);
     }
 }
 

@@ -158,3 +158,18 @@ ELUT_WORKLOAD_GROUPS = (
 def test_elut_fused_workload_groups(fmt, M, K, Ns):
     _announce("elut fused workload group", fmt, M, K, Ns)
     _elut_fused(fmt, M, K, Ns)
+
+
+# Where the MFMA form can go wrong: rows of less than one block, ragged last blocks, one row group, several batches of
+# a row group (K > 8192), token slices (more than 16 tokens, or as many as fit in LDS: 3 at K = 33024, 1 past 61000),
+# the 8-wave rows past 122000, with codes of both signs at their largest.
+@pytest.mark.parametrize("fmt", FMTS)
+@pytest.mark.parametrize("M,N,K", [(1, 16, 64), (5, 48, 192), (16, 16, 448), (17, 2080, 320), (33, 64, 4160),
+                                   (9, 48, 8512), (1, 4112, 4096), (8, 32, 33024), (2, 32, 61504), (1, 16, 132096),
+                                   (3, 32, 132096), (2, 4128, 960)])
+def test_elut_edges(fmt, M, N, K):
+    if fmt == "c3g5":
+        K = max(320, K // 320 * 320)
+    _announce("elut edges", fmt, M, N, K)
+    _vs_oracle(fmt, M, N, K, seed=inputs.seed_for(13, 700 + M * 31 + N + K))
+    _elut_fused(fmt, M, K, [N, 16])
