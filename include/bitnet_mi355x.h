@@ -160,8 +160,9 @@ size_t bitnet_mpgemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K
  *   prefill GEMM.  TL1: the same decode GEMV (the pair codes expanded to int8 in registers) where I2_S runs it;
  *   otherwise the weights are rewritten in the I2_S layout in the workspace (N * K / 4 bytes) for the prefill GEMM.
  *   Integer-weight layouts (C4G2, C5G2, C3G5): the group codes expanded to int8 and multiplied on int8 MFMA, up to 16
- *   tokens per slice and all slices in one launch, any M; x_rowsum is not used and no workspace is needed.  TL2_0 and TL1_0: the lossy table
- *   lookups described with the layouts, 8 tokens per launch, any M, no workspace; acc receives their integers.
+ *   tokens per slice and all slices in one launch, any M; x_rowsum is not used and no workspace is needed.  TL2_0 and
+ *   TL1_0: the lossy table lookups described with the layouts (from three tokens on as one-hot products on int8 MFMA, up
+ *   to 16 tokens per slice), any M, no workspace; acc receives their integers.
  *   TL2: one token runs the table lookups of Eq. 3 (tables built in LDS) where the row's tables fit (K <= 14336);
  *   otherwise, up to 16 tokens with 384 <= K < 18816, the packed triples are expanded to int8 weights and
  *   multiplied on int8 MFMA; more than 16 tokens (with N * K and M * K below 2^32) rewrite the weights in the

@@ -90,10 +90,10 @@ bitnet::FusedLinears one_linear(const void* packed, const float* w_scale, int64_
     return L;
 }
 
-// The table lookups of TL2, TL1 (lossy or not) for M tokens of already quantised activations: launches of up to 8
-// tokens, each over every weight of L (outputs of later slices offset by the slice's first token).
-hipError_t lookup_sliced(bool tl1, bool lossy, const bitnet::FusedLinears& L, const int8_t* xq, const float* x_scale,
-                         int64_t M, int64_t K, hipStream_t s) {
+// The table lookups of TL2 for M tokens of already quantised activations: launches of up to 8 tokens, each over every
+// weight of L (outputs of later slices offset by the slice's first token).
+hipError_t lookup_sliced(const bitnet::FusedLinears& L, const int8_t* xq, const float* x_scale, int64_t M, int64_t K,
+                         hipStream_t s) {
     for (int64_t m0 = 0; m0 < M; m0 += bitnet::kElutMaxTokens) {
         const int mc = (int)((M - m0) < bitnet::kElutMaxTokens ? (M - m0) : bitnet::kElutMaxTokens);
         bitnet::FusedLinears Ls = L;
@@ -101,11 +101,8 @@ hipError_t lookup_sliced(bool tl1, bool lossy, const bitnet::FusedLinears& L, co
             Ls.y[i] = L.y[i] + m0 * L.N[i];
             Ls.acc[i] = L.acc[i] ? L.acc[i] + m0 * L.N[i] : nullptr;
         }
-        const hipError_t e =
-            tl1 ? bitnet::launch_tl1_elut_decode(Ls, nullptr, xq + m0 * K, x_scale + m0, mc, (int)K, nullptr, nullptr,
-                                                 nullptr, s, lossy)
-                : bitnet::launch_tl2_elut_decode(Ls, nullptr, xq + m0 * K, x_scale + m0, mc, (int)K, nullptr, nullptr,
-                                                 nullptr, s, lossy);
+        const hipError_t e = bitnet::launch_tl2_elut_decode(Ls, nullptr, xq + m0 * K, x_scale + m0, mc, (int)K, nullptr,
+                                                            nullptr, nullptr, s, false);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -116,6 +113,16 @@ hipError_t lookup_sliced(bool tl1, bool lossy, const bitnet::FusedLinears& L, co
 bool tl2_via_i2s(int64_t M, int64_t N, int64_t K) {
     return M > kDecodeMaxTokens && (uint64_t)N * (uint64_t)K < ((uint64_t)1 << 32) &&
            (uint64_t)M * (uint64_t)K < ((uint64_t)1 << 32);
+}
+
+// TL2_0 / TL1_0 with the codes given: one and two tokens by table lookups, more as one-hot products on MFMA, up to 16
+// tokens a slice.  (Two tokens: one 100B-class layer takes 351 us by TL2_0 lookups and 439 as products, TL1_0 471 and 594;
+// from three on the products win everywhere, the 1B-class layers 55 -> 46 us, the 3B-class ones at four 94 -> 70.)
+hipError_t lossy_run(bool tl1, const bitnet::FusedLinears& L, const int8_t* xq, const float* x_scale, int64_t M, int64_t K,
+                     hipStream_t s) {
+    if (M > 2) return bitnet::launch_lossy(tl1, L, xq, x_scale, M, (int)K, s);
+    return tl1 ? bitnet::launch_tl1_elut_decode(L, nullptr, xq, x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s)
+               : bitnet::launch_tl2_elut_decode(L, nullptr, xq, x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s, true);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -255,8 +262,8 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
                          float* y, int32_t* acc, void* ws, size_t ws_bytes, hipStream_t s) {
     (void)packed_bytes;
     if (lossy_layout(layout)) {
-        // TL2_0 / TL1_0: table lookups on int8-quantised tables; one token on the persistent table kernels (every
-        // work group builds the row's tables once), else slices of 8 tokens
+        // TL2_0 / TL1_0: lookups in int8-quantised tables; one token on the persistent table kernels where the row's
+        // tables fit in LDS (every work group builds them once)
         if (layout == BITNET_LAYOUT_TL2_0 && M == 1 && bitnet::tl2_stream_fits((int)K))
             return hip_status(bitnet::launch_tl2_stream(one_linear(packed, w_scale, N, y, acc), nullptr, (int)K,
                                                         const_cast<int8_t*>(xq), const_cast<float*>(x_scale), nullptr,
@@ -267,8 +274,8 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
                                                               const_cast<int8_t*>(xq), const_cast<float*>(x_scale),
                                                               nullptr, s),
                               "bitnet_mpgemm launch");
-        return hip_status(lookup_sliced(layout == BITNET_LAYOUT_TL1_0, true, one_linear(packed, w_scale, N, y, acc),
-                                        xq, x_scale, M, K, s),
+        return hip_status(lossy_run(layout == BITNET_LAYOUT_TL1_0, one_linear(packed, w_scale, N, y, acc), xq, x_scale, M,
+                                    K, s),
                           "bitnet_mpgemm launch");
     }
     if (elut_layout(layout))   // the integer-weight formats expanded for MFMA, any M (slices of up to 16 tokens)
@@ -313,7 +320,7 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
         return hip_status(bitnet::launch_tl2_mfma_decode(one_linear(packed, w_scale, N, y, acc), xq, x_scale, (int)M,
                                                          (int)K, s),
                           "bitnet_mpgemm launch");
-    return hip_status(lookup_sliced(false, false, one_linear(packed, w_scale, N, y, acc), xq, x_scale, M, K, s),
+    return hip_status(lookup_sliced(one_linear(packed, w_scale, N, y, acc), xq, x_scale, M, K, s),
                       "bitnet_mpgemm launch");
 }
 
@@ -424,8 +431,7 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
 
     hipStream_t s = (hipStream_t)stream;
     if (elut_layout(layout) || lossy_layout(layout)) {
-        // every weight of the group in one table-lookup launch; one token quantised inside it, else the quantiser
-        // first (TL2_0 and TL1_0: launches of up to 8 tokens)
+        // every weight of the group in one launch; one token quantised inside it, else the quantiser first
         bitnet::FusedLinears L{};
         L.count = n_linears;
         int64_t rgs = 0;
@@ -451,20 +457,19 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
                               "bitnet_mpgemm_fused launch");
         if (quantise && M == 1) {
             const hipError_t e =
-                lossy_layout(layout)
-                    ? (tl1 ? bitnet::launch_tl1_elut_decode(L, x, nullptr, nullptr, 1, (int)K, xq, x_scale, x_rowsum, s,
-                                                            true)
-                           : bitnet::launch_tl2_elut_decode(L, x, nullptr, nullptr, 1, (int)K, xq, x_scale, x_rowsum, s,
-                                                            true))
-                    : bitnet::launch_elut(elut_format(layout), L, x, nullptr, nullptr, 1, (int)K, xq, x_scale,
-                                                  x_rowsum, s);
+                elut_layout(layout) ? bitnet::launch_elut(elut_format(layout), L, x, nullptr, nullptr, 1, (int)K, xq,
+                                                          x_scale, x_rowsum, s)
+                : tl1               ? bitnet::launch_tl1_elut_decode(L, x, nullptr, nullptr, 1, (int)K, xq, x_scale,
+                                                                     x_rowsum, s)
+                                    : bitnet::launch_tl2_elut_decode(L, x, nullptr, nullptr, 1, (int)K, xq, x_scale,
+                                                                     x_rowsum, s, true);
             return hip_status(e, "bitnet_mpgemm_fused launch");
         }
         hipError_t e = quantise ? bitnet::launch_quantize_act(x, M, K, xq, x_scale, x_rowsum, s) : hipSuccess;
         if (e == hipSuccess)
-            e = lossy_layout(layout) ? lookup_sliced(tl1, true, L, xq, x_scale, M, K, s)
-                                     : bitnet::launch_elut(elut_format(layout), L, nullptr, xq, x_scale, (int)M,
-                                                                   (int)K, nullptr, nullptr, nullptr, s);
+            e = lossy_layout(layout) ? lossy_run(tl1, L, xq, x_scale, M, K, s)
+                                     : bitnet::launch_elut(elut_format(layout), L, nullptr, xq, x_scale, (int)M, (int)K,
+                                                           nullptr, nullptr, nullptr, s);
         return hip_status(e, "bitnet_mpgemm_fused launch");
     }
     // the small-batch regime (17..128 tokens, K <= 16384): the decode GEMV in token slices, for I2_S and TL1

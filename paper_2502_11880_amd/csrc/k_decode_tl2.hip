@@ -340,13 +340,12 @@ __global__ __launch_bounds__(64 * WAVES) void tl2_elut_decode_kernel(
     }
 }
 
-// The TL1 layout by table lookup (Algorithm TL1; Table 5), one work group per 16-row group: wave w takes the 256-k
-// blocks w, w + WAVES, ... (four 64-k units each, the last block possibly fewer); lane l builds the 9-entry tables
-// of pair l % 32 of units l / 32 and 2 + l / 32, for a chunk of up to two tokens at a time, and lane (r, q) looks
-// up the 8 pairs of each of its block's words (row r, k = 64 j + 16 q .. + 15 of unit j).  LOSSY (TL1_0, Sec. 3.2.1):
-// each token's tables of a unit are quantised to int8 with the unit's power-of-two scale and the unit's sum is
-// scaled back.  Fused weight groups and QX as for the TL2 kernel.
-constexpr int kTl1BlockStride = 128 * kSlot;                 // the 128 pair tables of a 256-k block per token
+// One or two tokens of TL1_0 by table lookup (Algorithm TL1; Table 5; Sec. 3.2.1; one token where the row's tables do not
+// fit in LDS), one work group per 16-row group: wave w takes the 256-k blocks w, w + WAVES, ... (four 64-k units each, the last block
+// possibly fewer); lane l builds the 9-entry tables of pair l % 32 of units l / 32 and 2 + l / 32, quantised to int8 with
+// the unit's power-of-two scale, and lane (r, q) looks up the 8 pairs of each of its block's words (row r, k = 64 j +
+// 16 q .. + 15 of unit j); the unit's sum is scaled back.  Fused weight groups and QX as for the TL2 kernel.
+constexpr int kTl1BlockStride = 128 * kSlot;                 // the 128 pair tables of a 256-k block
 
 // Largest value of each half-wave (lanes 0..31 and 32..63) of v, as scalars: DPP maxima inside each row of 16 lanes,
 // then the four row results read from lanes 0, 16, 32 and 48.
@@ -357,7 +356,7 @@ __device__ __forceinline__ void half_wave_max(int v, int& lo, int& hi) {
     hi = max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48));
 }
 
-template <int WAVES, int MT, bool LOSSY, bool QX>
+template <int WAVES, int MT, bool QX>
 __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
     FusedLinears L, const float* __restrict__ x, const int8_t* __restrict__ xq, const float* __restrict__ x_scale,
     int M, int K, int8_t* __restrict__ xq_out, float* __restrict__ s_out, int32_t* __restrict__ rs_out) {
@@ -432,7 +431,7 @@ __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
                     b0 = xb[kSubK * u1];
                     b1 = xb[kSubK * u1 + 1];
                 }
-                if constexpr (LOSSY) {
+                {
                     int lo0, hi0, lo1, hi1;
                     half_wave_max(ok0 ? abs(a0) + abs(a1) : 0, lo0, hi0);
                     half_wave_max(ok1 ? abs(b0) + abs(b1) : 0, lo1, hi1);
@@ -445,12 +444,12 @@ __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
                 uint8_t* tj = lut + jj * kTl1BlockStride;
                 if (ok0) {
                     pair_table(a0, a1, w);
-                    if constexpr (LOSSY) quantize_words(w, hh ? sh[jj][1] : sh[jj][0]);
+                    quantize_words(w, hh ? sh[jj][1] : sh[jj][0]);
                     store_table(tj + (32 * hh + pr) * kSlot, w);
                 }
                 if (ok1) {
                     pair_table(b0, b1, w);
-                    if constexpr (LOSSY) quantize_words(w, hh ? sh[jj][3] : sh[jj][2]);
+                    quantize_words(w, hh ? sh[jj][3] : sh[jj][2]);
                     store_table(tj + (64 + 32 * hh + pr) * kSlot, w);
                 }
             }
@@ -1593,71 +1592,40 @@ hipError_t launch_elut_mt(const LookupArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <bool LOSSY>
-hipError_t launch_tl2_elut_lossy(const LookupArgs& a, hipStream_t stream) {
-    if (a.x) return launch_elut_mt<1, LOSSY, true>(a, stream);
-    if (a.M <= 1) return launch_elut_mt<1, LOSSY, false>(a, stream);
-    if (a.M <= 2) return launch_elut_mt<2, LOSSY, false>(a, stream);
-    if (a.M <= 4) return launch_elut_mt<4, LOSSY, false>(a, stream);
-    return launch_elut_mt<8, LOSSY, false>(a, stream);
-}
-
 hipError_t launch_tl2_elut_decode(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale,
                                   int M, int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream,
                                   bool lossy) {
     if (L.total <= 0) return hipSuccess;
-    if (M < 1 || M > 8 || (x && M != 1)) return hipErrorInvalidValue;
+    if (M < 1 || M > 8 || (lossy && M > 2) || (x && (M != 1 || !lossy))) return hipErrorInvalidValue;
     const LookupArgs a{&L, x, xq, x_scale, M, K, xq_out, s_out, rs_out};
-    return lossy ? launch_tl2_elut_lossy<true>(a, stream) : launch_tl2_elut_lossy<false>(a, stream);
-}
-
-// TL1 layout by table lookup (Algorithm TL1): the 32 pair tables of a 64-k unit per wave, lossy or not.
-int tl1_elut_waves(int M) {
-    const int tc = tl2_elut_chunk(M);
-    int w = 16;
-    while (w > 1 && (size_t)w * tc * kTl1BlockStride > (size_t)kElutLdsBudget) w >>= 1;
-    return w;
-}
-
-size_t tl1_elut_lds_bytes(int M) {
-    const size_t tables = (size_t)tl1_elut_waves(M) * tl2_elut_chunk(M) * kTl1BlockStride;
-    const size_t red = (size_t)tl1_elut_waves(M) * 16 * 16 * sizeof(int);
-    return tables > red ? tables : red;
-}
-
-template <int WAVES, int MT, bool LOSSY, bool QX>
-void launch_tl1_cfg(const LookupArgs& a, size_t lds, hipStream_t stream) {
-    hipLaunchKernelGGL((tl1_elut_decode_kernel<WAVES, MT, LOSSY, QX>), dim3((unsigned)a.L->total), dim3(64 * WAVES),
-                       lds, stream, *a.L, a.x, a.xq, a.x_scale, a.M, a.K, a.xq_out, a.s_out, a.rs_out);
-}
-
-template <int MT, bool LOSSY, bool QX>
-hipError_t launch_tl1_mt(const LookupArgs& a, hipStream_t stream) {
-    const size_t lds = tl1_elut_lds_bytes(a.M);
-    switch (tl1_elut_waves(a.M)) {
-        case 16: launch_tl1_cfg<16, MT, LOSSY, QX>(a, lds, stream); break;
-        case 8: launch_tl1_cfg<8, MT, LOSSY, QX>(a, lds, stream); break;
-        default: launch_tl1_cfg<4, MT, LOSSY, QX>(a, lds, stream); break;
+    if (lossy) {
+        if (x) return launch_elut_mt<1, true, true>(a, stream);
+        return M == 1 ? launch_elut_mt<1, true, false>(a, stream) : launch_elut_mt<2, true, false>(a, stream);
     }
-    return hipGetLastError();
+    if (M <= 1) return launch_elut_mt<1, false, false>(a, stream);
+    if (M <= 2) return launch_elut_mt<2, false, false>(a, stream);
+    if (M <= 4) return launch_elut_mt<4, false, false>(a, stream);
+    return launch_elut_mt<8, false, false>(a, stream);
 }
 
-template <bool LOSSY>
-hipError_t launch_tl1_elut_lossy(const LookupArgs& a, hipStream_t stream) {
-    if (a.x) return launch_tl1_mt<1, LOSSY, true>(a, stream);
-    if (a.M <= 1) return launch_tl1_mt<1, LOSSY, false>(a, stream);
-    if (a.M <= 2) return launch_tl1_mt<2, LOSSY, false>(a, stream);
-    if (a.M <= 4) return launch_tl1_mt<4, LOSSY, false>(a, stream);
-    return launch_tl1_mt<8, LOSSY, false>(a, stream);
-}
-
-hipError_t launch_tl1_elut_decode(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale,
-                                  int M, int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream,
-                                  bool lossy) {
+// One or two tokens of TL1_0: 16 waves, each with the 128 pair tables of a 256-k block per token (64 KiB a token).
+hipError_t launch_tl1_elut_decode(const FusedLinears& L, const float* x, const int8_t* xq, const float* x_scale, int M,
+                                  int K, int8_t* xq_out, float* s_out, int32_t* rs_out, hipStream_t stream) {
     if (L.total <= 0) return hipSuccess;
-    if (M < 1 || M > 8 || (x && M != 1)) return hipErrorInvalidValue;
-    const LookupArgs a{&L, x, xq, x_scale, M, K, xq_out, s_out, rs_out};
-    return lossy ? launch_tl1_elut_lossy<true>(a, stream) : launch_tl1_elut_lossy<false>(a, stream);
+    if (M < 1 || M > 2 || (x && M != 1)) return hipErrorInvalidValue;
+    constexpr int kWaves = 16;
+    const dim3 grid((unsigned)L.total), block(64 * kWaves);
+    const size_t lds = (size_t)kWaves * M * kTl1BlockStride;
+    if (x)
+        hipLaunchKernelGGL((tl1_elut_decode_kernel<kWaves, 1, true>), grid, block, lds, stream, L, x, xq, x_scale, M, K,
+                           xq_out, s_out, rs_out);
+    else if (M == 1)
+        hipLaunchKernelGGL((tl1_elut_decode_kernel<kWaves, 1, false>), grid, block, lds, stream, L, x, xq, x_scale, M, K,
+                           xq_out, s_out, rs_out);
+    else
+        hipLaunchKernelGGL((tl1_elut_decode_kernel<kWaves, 2, false>), grid, block, lds, stream, L, x, xq, x_scale, M, K,
+                           xq_out, s_out, rs_out);
+    return hipGetLastError();
 }
 
 size_t tl2_stream_lds_bytes(int K) {
@@ -1676,8 +1644,7 @@ hipError_t launch_stream_cfg(const FusedLinears& L, const float* x, int K, int8_
     const size_t lds = tl2_stream_lds_bytes(K);
     const void* kern = x ? reinterpret_cast<const void*>(tl2_stream_kernel<WAVES, U, XV, true, LOSSY>)
                          : reinterpret_cast<const void*>(tl2_stream_kernel<WAVES, U, XV, false, LOSSY>);
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WAVES, lds) != hipSuccess || occ <= 0) occ = 1;
+    const int occ = resident_groups(kern, 64 * WAVES, lds);
     const int64_t max_g = (int64_t)device_cus() * occ;
     const int64_t rounds = (L.total + max_g - 1) / max_g;
     const dim3 grid((unsigned)((L.total + rounds - 1) / rounds)), block(64 * WAVES);
@@ -1733,8 +1700,7 @@ hipError_t launch_tl1_stream_cfg(const FusedLinears& L, const float* x, int K, i
     const size_t lds = tl1_stream_lds_bytes(K);
     const void* kern = x ? reinterpret_cast<const void*>(tl1_lossy_stream_kernel<WAVES, U, XV, true>)
                          : reinterpret_cast<const void*>(tl1_lossy_stream_kernel<WAVES, U, XV, false>);
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WAVES, lds) != hipSuccess || occ <= 0) occ = 1;
+    const int occ = resident_groups(kern, 64 * WAVES, lds);
     const int64_t max_g = (int64_t)device_cus() * occ;
     const int64_t rounds = (L.total + max_g - 1) / max_g;
     const dim3 grid((unsigned)((L.total + rounds - 1) / rounds)), block(64 * WAVES);
@@ -1796,8 +1762,7 @@ hipError_t launch_mfma_kernel(const FusedLinears& L, const float* x, int8_t* xq,
                               int M, int K, hipStream_t stream) {
     const size_t lds = tl2_mfma_lds_bytes(M, K);
     const void* kern = reinterpret_cast<const void*>(tl2_mfma_decode_kernel<WAVES, U, CH, XV, MB>);
-    int occ = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kern, 64 * WAVES, lds) != hipSuccess || occ <= 0) occ = 1;
+    const int occ = resident_groups(kern, 64 * WAVES, lds);
     const int64_t max_g = (int64_t)device_cus() * occ;
     const int64_t rounds = (L.total + max_g - 1) / max_g;
     const dim3 grid((unsigned)((L.total + rounds - 1) / rounds)), block(64 * WAVES);

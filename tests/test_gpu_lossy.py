@@ -90,3 +90,28 @@ def test_lossy_fused_8b_groups(layout, M, K, Ns):
     _announce("lossy fused 8B-class", layout, M, K, Ns)
     from tests.test_gpu_fused import _fused_case_lossy
     _fused_case_lossy(layout, M, K, Ns, sample_groups=6)
+
+
+# Where the one-hot form can go wrong: every count of lanes that share a token's tables (1-4, 5-8, 9+ tokens) and of row
+# groups per work group (1, 2, 4, 8), the last work group's missing row groups, token slices past 16, a tail of five units
+# and of nothing else, and codes over the whole int8 range, so that blocks of every shift (entries up to 384: 0, 1, 2) and
+# ties of the rounding occur.
+@pytest.mark.parametrize("layout", ["tl2_0", "tl1_0"])
+@pytest.mark.parametrize("M,N,K", [(2, 48, 64), (3, 4112, 704), (4, 8240, 448), (5, 16, 1152), (7, 4128, 704),
+                                   (8, 8224, 384), (8, 17616, 704), (8, 33616, 448), (9, 48, 832), (13, 8240, 704),
+                                   (16, 17616, 448), (33, 80, 1600), (2, 33616, 448), (3, 17616, 64)])
+def test_lossy_edges(layout, M, N, K):
+    _announce("lossy edges", layout, M, N, K)
+    pack_ref, gemm_ref = _route(layout)
+    rng = np.random.default_rng(M * 7 + N + K)
+    W = inputs.weight_f32(N, K, seed=inputs.seed_for(15, 3 + M + N + K))
+    packed, w_scale = H.pack(W, layout)
+    # ranges of 40, 127 and 255 in turn over runs of 96 codes: blocks of every shift within one token
+    top = np.array([40, 127, 128])[(np.arange(K) // 96 + np.arange(M)[:, None]) % 3]
+    xq_np = np.clip(rng.integers(-128, 128, size=(M, K)), -top, np.minimum(top, 127)).astype(np.int8)
+    s_np = rng.uniform(0.5, 2.0, M).astype(np.float32)
+    y, acc = H.mpgemm(layout, packed, w_scale, N, K, torch.from_numpy(xq_np).to(H.DEV), torch.from_numpy(s_np).to(H.DEV))
+    t_ref, beta = O.ternarize(W.numpy())
+    acc_ref = gemm_ref(xq_np, pack_ref(t_ref), N, K)
+    assert np.array_equal(H.to_np(acc), acc_ref)
+    H.check_y(H.to_np(y), O.epilogue(acc_ref, beta, s_np), acc_ref)
