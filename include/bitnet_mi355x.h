@@ -155,10 +155,11 @@ size_t bitnet_mpgemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K
  *          nothing kept between calls.  Calls that run concurrently must not share it.
  *   Shapes: M >= 1, N % 16 == 0, K % 64 == 0, K <= 132096 (127 * K < 2^24 keeps acc exact in fp32);
  *   I2_S and TL1 also need N * K and M * K below 2^32.  I2_S: M <= 16 runs the decode GEMV; 17 <= M <= 112 with
- *   x_rowsum given and K <= 16384 runs the same GEMV in slices of up to 16 tokens, one launch for all slices (the
- *   small-batch regime between decode and prefill, which the paper leaves open, Sec. "Limitations"); larger M the
- *   prefill GEMM.  TL1: the same decode GEMV (the pair codes expanded to int8 in registers) where I2_S runs it;
- *   otherwise the weights are rewritten in the I2_S layout in the workspace (N * K / 4 bytes) for the prefill GEMM.
+ *   x_rowsum given and K <= 16384 runs the small-batch kernels (32-token tiles, or for short launches the GEMV in slices
+ *   of up to 16 tokens; the regime between decode and prefill, which the paper leaves open, Sec. "Limitations"); larger
+ *   M runs them where the prefill GEMM would split K and the problem is small, and the prefill GEMM otherwise.  TL1: the
+ *   same kernels (the pair codes expanded to int8 in registers) where I2_S runs them; otherwise the weights are
+ *   rewritten in the I2_S layout in the workspace (N * K / 4 bytes) for the prefill GEMM.
  *   Integer-weight layouts (C4G2, C5G2, C3G5): the group codes expanded to int8 and multiplied on int8 MFMA, up to 16
  *   tokens per slice and all slices in one launch, any M; x_rowsum is not used and no workspace is needed.  TL2_0 and
  *   TL1_0: the lossy table lookups described with the layouts (from three tokens on as one-hot products on int8 MFMA, up
@@ -166,7 +167,7 @@ size_t bitnet_mpgemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K
  *   TL2: one token runs the table lookups of Eq. 3 (tables built in LDS) where the row's tables fit (K <= 14336);
  *   otherwise, up to 16 tokens with 384 <= K < 18816, the packed triples are expanded to int8 weights and
  *   multiplied on int8 MFMA; more than 16 tokens (with N * K and M * K below 2^32) rewrite the weights in the
- *   I2_S layout in the workspace and run the I2_S prefill GEMM; the remaining shapes run the table lookups in
+ *   I2_S layout in the workspace and run what I2_S would; the remaining shapes run the table lookups in
  *   slices of 8 tokens.
  */
 bitnet_status bitnet_mpgemm(int layout, const void* packed, size_t packed_bytes, const float* w_scale,

@@ -282,11 +282,19 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
         return hip_status(bitnet::launch_elut(elut_format(layout), one_linear(packed, w_scale, N, y, acc), nullptr, xq,
                                               x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s),
                           "bitnet_mpgemm launch");
-    if (i2s_tiled(layout) && (M <= kDecodeMaxTokens || bitnet::i2s_sliced_ok(M, K, x_rowsum != nullptr)))
+    if (i2s_tiled(layout) && M <= kDecodeMaxTokens)
         return hip_status(bitnet::launch_i2s_decode(one_linear(packed, w_scale, N, y, acc), xq, x_scale, x_rowsum,
                                                     (int)M, (int)K, s, word_format(layout)),
                           "bitnet_mpgemm launch");
+    if (i2s_tiled(layout) && bitnet::i2s_sliced_ok(M, K, x_rowsum != nullptr))
+        return hip_status(bitnet::launch_smallbatch(one_linear(packed, w_scale, N, y, acc), xq, x_scale, x_rowsum,
+                                                    (int)M, (int)K, s, word_format(layout)),
+                          "bitnet_mpgemm launch");
     if (layout == BITNET_LAYOUT_TL1) {
+        const bitnet::FusedLinears L = one_linear(packed, w_scale, N, y, acc);
+        if (x_rowsum && bitnet::smallbatch_beats_prefill(L, M, K))      // reads TL1 words: nothing to rewrite
+            return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
+                              "bitnet_mpgemm launch");
         // the TL1 words rewritten as I2_S words at the start of the workspace, the GEMM's split-K slices after them
         const size_t wbytes = align256((size_t)N * (size_t)K / 4);
         const int n1 = (int)N;
@@ -472,7 +480,7 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
                                                            nullptr, nullptr, nullptr, s);
         return hip_status(e, "bitnet_mpgemm_fused launch");
     }
-    // the small-batch regime (17..128 tokens, K <= 16384): the decode GEMV in token slices, for I2_S and TL1
+    // the small-batch regime (17..112 tokens, K <= 16384), for I2_S and TL1
     const bool sliced = i2s_tiled(layout) && bitnet::i2s_sliced_ok(M, K, true);
     if (layout == BITNET_LAYOUT_I2S || (layout == BITNET_LAYOUT_TL1 && (M <= kDecodeMaxTokens || sliced))) {
         const int fmt = word_format(layout);
@@ -494,9 +502,9 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
                               "bitnet_mpgemm_fused launch");
         hipError_t e = quantise ? bitnet::launch_quantize_act(x, M, K, xq, x_scale, x_rowsum, s) : hipSuccess;
         if (e == hipSuccess)
-            e = (M <= kDecodeMaxTokens || sliced)
-                    ? bitnet::launch_i2s_decode(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, fmt)
-                    : bitnet::launch_i2s_prefill(L, xq, x_scale, x_rowsum, (int)M, (int)K, ws, ws_bytes, s);
+            e = M <= kDecodeMaxTokens ? bitnet::launch_i2s_decode(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, fmt)
+                : sliced ? bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, fmt)
+                         : bitnet::launch_i2s_prefill(L, xq, x_scale, x_rowsum, (int)M, (int)K, ws, ws_bytes, s);
         return hip_status(e, "bitnet_mpgemm_fused launch");
     }
     // TL2: one token: one launch for every weight that quantises inside (the MFMA expansion, or the table lookups
@@ -537,6 +545,9 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
         words += align256((size_t)N[i] * (size_t)K / 4);
     }
     if (via && ws_bytes >= words) {
+        if (!tl2 && bitnet::smallbatch_beats_prefill(L, M, K))          // reads TL1 words: nothing to rewrite
+            return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
+                              "bitnet_mpgemm_fused launch");
         bitnet::FusedLinears T = L;
         size_t off = 0;
         void* dst[bitnet::kMaxFused];
