@@ -292,7 +292,7 @@ bitnet_status mpgemm_run(int layout, const void* packed, size_t packed_bytes, co
                           "bitnet_mpgemm launch");
     if (layout == BITNET_LAYOUT_TL1) {
         const bitnet::FusedLinears L = one_linear(packed, w_scale, N, y, acc);
-        if (x_rowsum && bitnet::smallbatch_beats_prefill(L, M, K))      // reads TL1 words: nothing to rewrite
+        if (x_rowsum && bitnet::smallbatch_beats_prefill(L, M, K, true))      // reads TL1 words: nothing to rewrite
             return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
                               "bitnet_mpgemm launch");
         // the TL1 words rewritten as I2_S words at the start of the workspace, the GEMM's split-K slices after them
@@ -545,7 +545,7 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
         words += align256((size_t)N[i] * (size_t)K / 4);
     }
     if (via && ws_bytes >= words) {
-        if (!tl2 && bitnet::smallbatch_beats_prefill(L, M, K))          // reads TL1 words: nothing to rewrite
+        if (!tl2 && bitnet::smallbatch_beats_prefill(L, M, K, true))          // reads TL1 words: nothing to rewrite
             return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
                               "bitnet_mpgemm_fused launch");
         bitnet::FusedLinears T = L;

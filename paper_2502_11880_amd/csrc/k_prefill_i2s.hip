@@ -537,12 +537,15 @@ size_t prefill_workspace_bytes(const FusedLinears& L, int64_t M, int64_t K) {
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)total_rows(L) * sizeof(int32_t) : 0;
 }
 
-// Where the GEMM would split K (its tiles leave half the CUs idle or more), small problems run on the small-batch kernels:
-// up to 280 32-row x 32-token x 256-k blocks a CU (us, I2_S, GEMM against small batch: q + k + v of the 8B class at 120 /
-// 512 tokens 26.7 / 11.0 and 31.8 / 22.4; o at 1024 34.3 / 29.2; its down projection, K = 14336, at 256 / 320 tokens 31.7 /
-// 25.1 and 35.7 / 34.5; past the line 8640 -> 3200 rows at 768 tokens 37.3 / 38.6, down at 768 55.8 / 62.7).  Without a
-// split the GEMM's tiles are the better ones (8640 + 8640 rows, K = 3200, at 256 tokens 25.9 / 30.3).
-bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K) {
+// Where the GEMM would split K (its tiles leave half the CUs idle or more), small problems run on the small-batch
+// kernels: up to 280 32-row x 32-token x 256-k blocks a CU (us, I2_S, GEMM / small batch: q + k + v of the 8B class at
+// 120 and 512 tokens 26.7 / 11.0 and 31.8 / 22.4; o at 1024 34.3 / 29.2; its down projection, K = 14336, at 256 and 320
+// tokens 31.7 / 25.1 and 35.7 / 34.5; past the line 8640 -> 3200 rows at 768 tokens 37.3 / 38.6, down at 768 55.8 /
+// 62.7).  Without a split the GEMM's tiles are the better ones (8640 + 8640 rows, K = 3200, at 256 tokens 25.9 / 30.3),
+// unless the weights would be rewritten for them: TL1 up to 256 tokens (gate + up at 192 and 256 tokens 52.0 / 42.5 and
+// 53.2 / 51.1; 8640 + 8640 rows at 256 37.8 / 33.2).
+bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite) {
+    if (rewrite && M <= 256) return true;
     int wn, splits;
     prefill_plan(L, M, K, wn, splits);
     int64_t tiles = 0;
@@ -552,7 +555,7 @@ bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K) {
 
 hipError_t launch_i2s_prefill(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
                               int M, int K, void* ws, size_t ws_bytes, hipStream_t stream) {
-    if (x_rowsum && smallbatch_beats_prefill(L, M, K))
+    if (x_rowsum && smallbatch_beats_prefill(L, M, K, false))
         return launch_smallbatch(L, xq, x_scale, x_rowsum, M, K, stream, kFmtI2s);
     int wn, splits;
     prefill_plan(L, M, K, wn, splits);

@@ -59,11 +59,11 @@ def test_small_batch_fused(layout, M, K, Ns):
 # Every tile shape of the small-batch kernels at its edges (32-row x 32-token tiles t against 256 CUs): 32 rows with 4 and
 # 8 waves, 64 rows with 8 waves (256 < t <= 512) and 4 (to 1024), the wide kernel (past 1024; odd and even numbers of
 # 512-k stages); short last blocks of 1, 2 and 3 sub-tiles; row counts that end inside a tile; one token past a tile;
-# past 112 tokens the launches that leave the prefill GEMM (TL2 through its rewritten words).  Sums are exact integers.
+# past 112 tokens the launches that leave the prefill GEMM, and TL1 at its last 256 tokens and one past (TL2 through its rewritten words).  Sums are exact integers.
 @pytest.mark.parametrize("layout", ["i2s", "tl1"])
 @pytest.mark.parametrize("M,N,K", [(65, 304, 704), (97, 48, 1088), (49, 4176, 2112), (112, 5136, 1152),
                                    (112, 8304, 1216), (65, 11024, 1088), (112, 10256, 192), (129, 208, 1344),
-                                   (300, 528, 832)])
+                                   (300, 528, 832), (256, 9216, 576), (257, 4128, 320)])
 def test_small_batch_shapes(layout, M, N, K):
     _announce("small batch shape", layout, M, N, K)
     _vs_oracle(layout, M, N, K, seed=inputs.seed_for(14, 3000 + M + N + K))
