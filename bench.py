@@ -20,8 +20,9 @@ bound "hbm".  Prefill: `value` = int8 TOP/s of the step (2*M*N*K per linear), `r
 10th/50th/90th percentile of the per-step time over ten replays of the same graph (the first is the timed one).
 `cpu_baseline` times the CPU oracle on a bounded sample of the same workload, with every host thread and with one.
 `parity` checks the timed launches themselves (the first activation group's fused call, in the first, middle and
-last layer) on every output against the oracle.  The default run also measures the 8B-class layer set at 2048 tokens
-(I2_S prefill) in a child process started first and adds it as `prefill_extra` (`--no-extra` skips it).
+last layer) on every output against the oracle; the run exits with status 3 where the check fails.  The default
+run also measures the 8B-class layer set at 2048 tokens (I2_S prefill) in a child process started first and adds
+it as `prefill_extra` (`--no-extra` skips it).
 """
 from __future__ import annotations
 
@@ -38,6 +39,7 @@ ROT_BYTES = 512 << 20            # rotate through at least 2x the Infinity Cache
 DECODE_MAX_TOKENS = 16
 SMALL_BATCH_MAX = 112            # 17..112 tokens: the decode GEMV in token slices (I2_S, TL1)
 CPU_ROWS = 512                   # oracle timing sample per weight for stacks of layers
+PARITY_EXIT = 3                  # exit status of a run whose figures stand beside a failed parity check
 METRIC = "decode GEMV weight GB/s (% HBM peak) + tokens/s; prefill int8 TOPS (% MFMA peak)"
 
 
@@ -56,6 +58,12 @@ def parse():
     p.add_argument("--no-parity", action="store_true")
     p.add_argument("--replays", type=int, default=10, help="replays of the timed graph for the spread figure")
     return p.parse_args()
+
+
+def exit_code(out):
+    """0, or PARITY_EXIT where a parity check of the printed line failed (the line's own, or the prefill figure's)."""
+    checks = [(out.get("parity") or {}).get("pass"), (out.get("prefill_extra") or {}).get("parity_pass")]
+    return PARITY_EXIT if False in checks else 0
 
 
 def log(msg):
@@ -103,7 +111,8 @@ def prefill_extra(args):
         cmd.append("--no-parity")
     try:
         res = subprocess.run(cmd, stdout=subprocess.PIPE, text=True, timeout=600)
-        line = [ln for ln in res.stdout.splitlines() if ln.startswith("{")][-1] if res.returncode == 0 else None
+        lines = [ln for ln in res.stdout.splitlines() if ln.startswith("{")]
+        line = lines[-1] if res.returncode in (0, PARITY_EXIT) else None
     except (subprocess.TimeoutExpired, IndexError):
         line = None
     if line is None:
@@ -372,6 +381,7 @@ def main():
     if extra is not None:
         out["prefill_extra"] = extra
     print(json.dumps(out), flush=True)
+    sys.exit(exit_code(out))
 
 
 # committed counter summaries (HBM bytes per launch) and the kernel sources they were taken on
@@ -440,10 +450,12 @@ def parity_check(args, layout, M, linears, groups, by_name, xs, ys, fargs, n_lay
     rs = torch.empty(M, dtype=torch.int32, device=dev)
     layers = sorted({0, n_layers // 2, n_layers - 1})
     codes_ok, zeros_ok, worst, outputs = True, True, 0.0, 0
+    # everything the call touches is ordered on its own stream: a fill left on another one may land after its stores
+    stream.wait_stream(torch.cuda.current_stream())
     for l in layers:
-        for n in g:
-            ys[n].fill_(float("nan"))
         with torch.cuda.stream(stream):
+            for n in g:
+                ys[n].fill_(float("nan"))
             B.bitnet_mpgemm_fused(layout, None, None, xs[0], xq, s, rs, None, ws, stream.cuda_stream,
                                   args=fargs[0][l][0])
         torch.cuda.synchronize()
