@@ -203,15 +203,27 @@ __global__ __launch_bounds__(kMeanThreads) void absmean_kernel(const float4* __r
 // quotient is at most 0.5, which rounds to 0.  The next fp32 above beta / 2 is at least beta / 2 (1 + 2^-24) away from
 // it relatively (2^-23 significands have 24 bits), strictly more than the 0.5 + 2^-25 that still rounds to 0.5; of a
 // subnormal beta of n units it is (n + 1) / 2 units or more, further off still.  2 |w| is exact (or infinite, and then
-// above every finite beta).  beta = 0 gives 0.
+// above every finite beta).  beta = 0 gives 0.  Weights that are not finite keep what the division gives under
+// clamp = fmin(fmax(., -1), 1): NaN is -1, and so is every weight where beta is NaN; where beta is infinite a finite
+// weight is 0 and an infinite one (inf / inf) -1.
 constexpr int kPackWaves = 4;
 
-__device__ __forceinline__ uint32_t code_of(float w, float thr) {
-    const float a = fabsf(w);
-    return (a + a <= thr) ? 1u : (w > 0.0f ? 2u : 0u);
+// code_of a weight w: 1 where scale |w| <= thr, else 2 where w > low, else 0.
+struct Threshold {
+    float scale, thr, low;
+    __device__ __forceinline__ explicit Threshold(float beta) {
+        const bool finite = beta < __builtin_inff();           // false for NaN
+        scale = finite ? 2.0f : 1.0f;
+        thr = beta == 0.0f ? __builtin_inff() : finite ? beta : beta == __builtin_inff() ? 0x1.fffffep127f : beta;
+        low = finite ? 0.0f : __builtin_inff();
+    }
+};
+
+__device__ __forceinline__ uint32_t code_of(float w, const Threshold& t) {
+    return fabsf(w) * t.scale <= t.thr ? 1u : w > t.low ? 2u : 0u;
 }
-__device__ __forceinline__ uint32_t codes4(const float4& v, float thr) {
-    return code_of(v.x, thr) | (code_of(v.y, thr) << 8) | (code_of(v.z, thr) << 16) | (code_of(v.w, thr) << 24);
+__device__ __forceinline__ uint32_t codes4(const float4& v, const Threshold& t) {
+    return code_of(v.x, t) | (code_of(v.y, t) << 8) | (code_of(v.z, t) << 16) | (code_of(v.w, t) << 24);
 }
 
 // 4 bytes below 16 as 16 bits, byte 0 lowest
@@ -240,8 +252,7 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_i2s_tiles(const float* _
     const size_t R = d / (size_t)nblk;
     const int s = (int)(d - R * (size_t)nblk);
     const int T = min(4, K / kSubK - 4 * s);
-    const float beta = *beta_p;
-    const float thr = beta == 0.0f ? __builtin_inff() : beta;
+    const Threshold thr(*beta_p);
     uint8_t* ts = tile_s[wave];
     const float* src = W + R * kRowsPerGroup * (size_t)K + (size_t)s * kI2sBlockK + 4 * min(lane, 16 * T - 1);
     float4 v[kRowsPerGroup];
@@ -310,8 +321,7 @@ __global__ __launch_bounds__(64 * kPackWaves) void pack_tl2_tiles(const float* _
     const int per_rg = nblk + (units ? 1 : 0);
     const size_t R = d / (size_t)per_rg;
     const int blk = (int)(d - R * (size_t)per_rg);
-    const float beta = *beta_p;
-    const float thr = beta == 0.0f ? __builtin_inff() : beta;
+    const Threshold thr(*beta_p);
     uint8_t* ts = tile_s[wave];
     const float* src = W + R * kRowsPerGroup * (size_t)K + (size_t)blk * kTl2BlockK;
     const int r = lane & 15, q = lane >> 4;

@@ -66,6 +66,58 @@ def test_pack_beta_and_bytes(layout, kind, N, K):
     assert np.array_equal(H.to_np(packed), PACK[layout](t_ref))
 
 
+def _mean_bits(W):
+    """The bits of the mean as the packer defines it for every bit pattern: the significands (with the implicit bit, also
+    for exponent 255) weigh 2^(e - 150), their exact mean is rounded to 24 bits, ties to even, and put together as
+    (E + 126) 2^23 + significand, so that a mean of 2^128 has the bits of infinity and a larger one of a NaN."""
+    b = np.abs(W).view(np.uint32).astype(np.int64).ravel()
+    e, m = b >> 23, b & 0x7FFFFF
+    total = sum(int(s) << int(x) for x, s in zip(np.maximum(e, 1), m + (e > 0) * (1 << 23)))    # in units of 2^-150
+    den = len(b) << 1                                        # the mean in units of 2^-149
+    top = (total // den).bit_length()                        # normal: at least 24 bits
+    sh = max(top - 24, 0)
+    q, r = divmod(total, den << sh)
+    q += 2 * r > (den << sh) or (2 * r == (den << sh) and q & 1)
+    return (sh << 23) + q if top >= 24 else q
+
+
+def _division_codes(W, beta):
+    with np.errstate(all="ignore"):
+        r = np.rint(W / beta)
+    return np.where(np.isnan(r), -1, np.clip(r, -1, 1)).astype(np.int8)
+
+
+# The last kind of weights has a finite mean; the others' means are infinite or NaN.
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", list(PACK))
+@pytest.mark.parametrize("kind,beta_is", [("inf", np.isinf), ("mostly_inf", np.isinf), ("nan", np.isnan),
+                                          ("mostly_nan", np.isnan), ("few", np.isfinite)])
+def test_pack_weights_that_are_not_finite(layout, kind, beta_is):
+    print("case: pack", layout, kind, flush=True)
+    N, K = 32, 704
+    W = _gauss(N, K).copy()
+    f = W.ravel()
+    if kind == "inf":
+        W = np.copysign(np.float32(np.inf), W)
+    elif kind == "mostly_inf":                               # the largest finite weights keep the mean at 2^128
+        f[1:] = np.copysign(np.float32(np.inf), f[1:])
+        f[0] = np.float32(3.4028235e38)
+    elif kind == "nan":
+        f[:] = np.copysign(np.float32(np.nan), f)
+    elif kind == "mostly_nan":                               # NaN of the largest significand: the mean stays above 2^128
+        f.view(np.uint32)[:] |= 0x7FFFFFFF
+        f[::3] = np.copysign(np.float32(0.02), _gauss(N, K).ravel()[::3])
+    else:
+        f[5], f[6], f[700], f[1400] = np.inf, -np.inf, np.nan, -np.nan
+    packed, beta = H.pack(torch.from_numpy(W), layout)
+    bits = int(H.to_np(beta).view(np.uint32)[0])
+    assert bits == _mean_bits(W)
+    b = np.uint32(bits).view(np.float32)
+    assert beta_is(b)
+    t = _division_codes(W, b)
+    assert np.array_equal(H.to_np(packed), PACK[layout](t))
+
+
 def test_threshold_equals_the_rounded_division():
     """clamp(rint(fp32(w / beta)), -1, 1) == 0 exactly where 2 |w| <= beta, for normal and subnormal beta, with w at and
     around beta / 2."""
