@@ -382,13 +382,23 @@ SmallLinears tile_linears(const FusedLinears& L, int rows) {
     return P;
 }
 
+// A launch holds less than 2^32 threads: 2^28 rows at 97 tokens (eight weights of K = 64) are past it, so the token slices
+// go in as many launches as that takes (one slice of every row that the entry points accept fits).
 template <int FMT>
 void launch_wide(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum, int M, int K,
                  hipStream_t stream) {
-    const SmallLinears P = tile_linears(L, 128);
-    const int slices = (M + kTok - 1) / kTok;
-    hipLaunchKernelGGL((smallbatch_wide_kernel<FMT>), dim3((unsigned)(P.tiles * slices)), dim3(512), 0, stream, P, xq,
-                       x_scale, x_rowsum, M, K, slices);
+    constexpr int64_t kThreads = 512, kMaxGroups = 0xffffffffLL / kThreads;
+    SmallLinears P = tile_linears(L, 128);
+    const int64_t most = kMaxGroups / P.tiles * kTok;             // tokens of one launch
+    for (int64_t m0 = 0; m0 < M; m0 += most) {
+        const int mc = (int)(M - m0 < most ? M - m0 : most), slices = (mc + kTok - 1) / kTok;
+        for (int i = 0; i < L.count; ++i) {
+            P.L.y[i] = L.y[i] + m0 * L.N[i];
+            P.L.acc[i] = L.acc[i] ? L.acc[i] + m0 * L.N[i] : nullptr;
+        }
+        hipLaunchKernelGGL((smallbatch_wide_kernel<FMT>), dim3((unsigned)(P.tiles * slices)), dim3(kThreads), 0, stream, P,
+                           xq + m0 * K, x_scale + m0, x_rowsum + m0, mc, K, slices);
+    }
 }
 
 template <int NT, int WAVES, int FMT>

@@ -76,3 +76,25 @@ def test_small_batch_fused_shapes(layout, M, K, Ns):
     _announce("small batch fused shape", layout, M, K, Ns)
     from tests.test_gpu_fused import _fused_case
     _fused_case(layout, M, K, Ns, seed=inputs.seed_for(14, 4000 + M + K + len(Ns)))
+
+
+# 2^28 rows at 112 tokens: 2^32 threads of the wide kernel in one launch would be one too many, so the tokens go in two.
+# Every weight is the same 16 rows over and over, so one small product is the whole oracle.
+@pytest.mark.parametrize("layout", ["i2s", "tl1"])
+def test_small_batch_more_rows_than_one_launch_holds(layout):
+    _announce("small batch, 2^28 rows", layout)
+    M, N, K, count = 112, 1 << 25, 64, 8
+    W = inputs.weight_f32(16, K, seed=inputs.seed_for(14, 5000))
+    x = inputs.activation_f32(M, K, seed=inputs.seed_for(14, 5001))
+    tile, scale = H.pack(W, layout)
+    packed = tile.repeat(N // 16)
+    xq, s, rs = H.quantize(x, with_rowsum=True)
+    y = torch.full((M, N), float("nan"), device=H.DEV)           # every weight of the call writes the same values here
+    ws = torch.empty(max(16, B.bitnet_mpgemm_fused_workspace_bytes(layout, [N] * count, K, M)), dtype=torch.uint8,
+                     device=H.DEV)
+    B.bitnet_mpgemm_fused(layout, [packed] * count, [scale] * count, None, xq, s, rs, [y] * count, ws=ws)
+    y_ref, acc_ref, *_ = O.mpgemm_reference(x.numpy(), W.numpy())
+    first = y[:, :16].clone()
+    H.check_y(H.to_np(first), y_ref, acc_ref)
+    for m in range(M):
+        assert bool((y[m].view(-1, 16) == first[m]).all()), m
