@@ -228,12 +228,23 @@ constexpr int kSmallBatchMaxTokens = 112;   // past it the small-batch kernels r
 inline bool i2s_sliced_ok(int64_t M, int64_t K, bool has_rowsum) {
     return M > 16 && M <= kSmallBatchMaxTokens && has_rowsum && K <= 16384;
 }
+// Tokens of one slice: up to 16 (one MFMA's rows), as many as keep their codes in 128 KiB of LDS, at least 4.
+constexpr int64_t kDecodeStageBytes = 128 * 1024;
+inline int decode_slice_tokens(int64_t K) {
+    int slice = 16;
+    while (slice > 4 && slice * (K + 16) > kDecodeStageBytes) slice -= 4;
+    return slice;
+}
 hipError_t launch_i2s_decode(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
                              int M, int K, hipStream_t stream, int fmt = kFmtI2s);
-// 17 tokens and more of either word format (k_smallbatch.hip), x_rowsum given; short launches of up to 64 tokens go on to
-// launch_i2s_decode's slices.
+// 17 tokens and more of either word format (k_smallbatch.hip), x_rowsum given; launches of few rows, up to 112 tokens and
+// K <= 16384, go on to launch_i2s_decode's slices.
 hipError_t launch_smallbatch(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
                              int M, int K, hipStream_t stream, int fmt);
+// The route launch_smallbatch takes (0: launch_i2s_decode's token slices; 1..4: tiles of 32 rows with 4 and 8 waves, of 64
+// rows with 8 and 4; 5: the wide kernel), and its estimated time in us.
+int smallbatch_route(const FusedLinears& L, int64_t M, int64_t K);
+double smallbatch_us(const FusedLinears& L, int64_t M, int64_t K);
 // Whether a launch that would go to the prefill GEMM is faster on the small-batch kernels; rewrite: the GEMM would need its
 // weights rewritten first (TL1).
 bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite);

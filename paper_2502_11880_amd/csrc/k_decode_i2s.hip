@@ -587,8 +587,6 @@ void launch_plain_u(int U, const FusedLinears& L, const int8_t* xq, const float*
     else launch_plain<FMT, WAVES, 4>(L, xq, x_scale, x_rowsum, M, K, stream);
 }
 
-constexpr int64_t kDecodeStageBytes = 128 * 1024;   // LDS for the tokens' codes in the multi-token stream
-
 template <int FMT, int WAVES, int U, int XV, bool AREG = false>
 hipError_t launch_stream(const FusedLinears& L, const float* x, int K, int8_t* xq, float* s, int32_t* rs,
                          hipStream_t stream) {
@@ -726,9 +724,7 @@ hipError_t launch_decode_fmt(const FusedLinears& L, const int8_t* xq, const floa
                              int M, int K, hipStream_t stream) {
     const int nkb = (K + kI2sBlockK - 1) / kI2sBlockK;
     const int cus = device_cus();
-    // tokens per work group: up to 16 (one MFMA's rows), as many as fit in LDS; more tokens run as token slices
-    int slice = 16;
-    while (slice > 4 && (int64_t)slice * (K + 16) > kDecodeStageBytes) slice -= 4;
+    const int slice = decode_slice_tokens(K);                 // tokens per work group; more tokens run as token slices
     const int per = M < slice ? M : slice;
     const bool fits = (int64_t)per * (K + 16) <= kDecodeStageBytes;   // a slice's codes fit in LDS
     if (M > 16 && !(x_rowsum && fits && nkb <= 64)) return hipErrorInvalidValue;

@@ -537,20 +537,24 @@ size_t prefill_workspace_bytes(const FusedLinears& L, int64_t M, int64_t K) {
     return splits > 1 ? (size_t)splits * (size_t)M * (size_t)total_rows(L) * sizeof(int32_t) : 0;
 }
 
-// Where the GEMM would split K (its tiles leave half the CUs idle or more), small problems run on the small-batch
-// kernels: up to 280 32-row x 32-token x 256-k blocks a CU (us, I2_S, GEMM / small batch: q + k + v of the 8B class at
-// 120 and 512 tokens 26.7 / 11.0 and 31.8 / 22.4; o at 1024 34.3 / 29.2; its down projection, K = 14336, at 256 and 320
-// tokens 31.7 / 25.1 and 35.7 / 34.5; past the line 8640 -> 3200 rows at 768 tokens 37.3 / 38.6, down at 768 55.8 /
-// 62.7).  Without a split the GEMM's tiles are the better ones (8640 + 8640 rows, K = 3200, at 256 tokens 25.9 / 30.3),
-// unless the weights would be rewritten for them: TL1 up to 256 tokens (gate + up at 192 and 256 tokens 52.0 / 42.5 and
-// 53.2 / 51.1; 8640 + 8640 rows at 256 37.8 / 33.2).
+// Where the GEMM would split K (its tiles leave half the CUs idle or more), the launch runs where the estimate is lower.
+// The GEMM's: its start and the finish pass, 1.3 us per 256-k stage of a slice, and the int32 slices (fitted to 340
+// launches, one in six off by more than 7%).  Measured, us, I2_S, GEMM / small batch: q + k + v of the 8B class at 120 and
+// 512 tokens 26.7 / 11.0 and 31.8 / 22.4; its down projection, K = 14336, at 256 tokens 31.7 / 25.1 and at 768 55.8 / 62.7;
+// 9024 rows of K = 26752 at 34 tokens 37.8 / 46.6, 7488 of 22720 at 67 35.5 / 42.6.  Without a split the GEMM's tiles are the
+// better ones (8640 + 8640 rows, K = 3200, at 256 tokens 25.9 / 30.3), unless the weights would be rewritten for them: TL1
+// up to 256 tokens (gate + up at 192 tokens 52.0 / 42.5; 8640 + 8640 rows at 256 37.8 / 33.2), but not in the last 32 of these,
+// where the GEMM's second tile of tokens is full, with K <= 4096 and 80 rows a CU or more (32224 + 32224 rows of K = 1472 at
+// 253 tokens 50.9 / 60.4, 23792 + 23792 of 1664 at 248 46.7 / 50.9).
 bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite) {
-    if (rewrite && M <= 256) return true;
     int wn, splits;
     prefill_plan(L, M, K, wn, splits);
-    int64_t tiles = 0;
-    for (int i = 0; i < L.count; ++i) tiles += (L.N[i] + 31) / 32;
-    return splits > 1 && tiles * ((M + 31) / 32) * ((K + kBK - 1) / kBK) <= 280 * (int64_t)device_cus();
+    if (rewrite && M <= 256) return splits > 1 || M <= 224 || K > 16 * kBK || total_rows(L) < 80 * (int64_t)device_cus();
+    if (splits == 1) return false;
+    const int64_t nkb = (K + kBK - 1) / kBK, rows = total_rows(L);
+    const double gemm = 13.47 + 1.30 * (double)((nkb + splits - 1) / splits) + 0.38e-6 * 4.0 * splits * (double)(M * rows);
+    const double rewritten = rewrite ? 3.0 + 0.8e-6 * (double)(rows * K / 4) : 0.0;
+    return smallbatch_us(L, M, K) < gemm + rewritten;
 }
 
 hipError_t launch_i2s_prefill(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,

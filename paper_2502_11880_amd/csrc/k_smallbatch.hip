@@ -18,6 +18,7 @@
 // The next block's loads are in flight while the current one multiplies.
 #include "bitnet_internal.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace bitnet {
@@ -410,44 +411,100 @@ void launch_tile(const FusedLinears& L, const int8_t* xq, const float* x_scale, 
                        stream, P, xq, x_scale, x_rowsum, M, K, slices);
 }
 
-// The shape, by t = 32-row x 32-token tiles in the launch against the CUs (us, I2_S, K = 4096 unless given; the 8B- and
-// 3B-class groups):
+// The routes of a small batch: the shapes of the tile kernels, and the token slices of the decode GEMV.
+enum Route { kGemvSlices, kTiles32x4, kTiles32x8, kTiles64x8, kTiles64x4, kTilesWide };
+
+// The tile shape, by t = 32-row x 32-token tiles in the launch against the CUs (us, I2_S, K = 4096 unless given; the 8B-
+// and 3B-class groups):
 //   t <= CUs      32 rows, 8 waves: every tile on a CU of its own (down projection, K = 14336, 45 tokens: 12.0 against
 //                 14.5 with 64 rows, 14.2 with 4 waves, 20.0 as token slices of the GEMV)
 //   t <= 2 CUs    64 rows, 8 waves: still one round (q + k + v at 45 tokens: 7.4; 32 rows 8.6, GEMV 8.4)
 //   t <= 4 CUs    64 rows, 4 waves: several groups to a CU, one's start under another's stream (gate + up at 32 tokens:
 //                 12.6; 8 waves 15.0, wide 12.7, GEMV 15.5)
 //   more          the wide kernel (gate + up at 45 tokens: 16.2; 64 rows 19.1, GEMV 22.7)
-// Up to four blocks of K have no work for a fifth wave: 32 rows, 4 waves.  The GEMV's slices stay for short launches,
-// whose time is their start (the lighter kernel), in the four regions of K where they measured ahead, GEMV / these:
-//   K <= 1024   many tiles, up to 64 tokens: 3072 + 3072 rows at 18 / 45 tokens 4.0 / 4.2 and 4.8 / 5.0
-//   to 2048     2048 + 512 + 512 rows at 17 tokens 4.0 / 4.7; 4608 + 4608 rows, K = 1536, at 33 tokens 6.2 / 7.1
-//   to 4096     o projection at 18 tokens 5.4 / 5.7; 3072 -> 1024 rows at 45 tokens 4.7 / 5.3
-//   to 8192     8192 -> 2560 rows at 24 tokens 6.9 / 7.9; past it its slices of 12 or 8 tokens read the words once more
-//               (8640 -> 3200 rows at 18 tokens 9.6 / 8.2)
-template <int FMT>
-hipError_t launch_fmt(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum, int M,
-                      int K, hipStream_t stream) {
+// Up to four blocks of K have no work for a fifth wave: 32 rows, 4 waves.
+Route tile_route(const FusedLinears& L, int64_t M, int64_t K) {
     const int64_t cus = device_cus();
     int64_t t = 0;
     for (int i = 0; i < L.count; ++i) t += (L.N[i] + 31) / 32;
     t *= (M + kTok - 1) / kTok;
-    const bool shortk = K <= 4 * kI2sBlockK;
-    const bool one = M <= kTok;
-    const bool gemv = shortk                 ? M <= 64 && 2 * t > cus
-                      : K <= 8 * kI2sBlockK  ? (one ? t > 48 && 2 * t <= cus : M <= 48 && 2 * t > cus)
-                      : K <= 16 * kI2sBlockK ? M <= 64 && (one ? 2 : 4) * t <= cus
-                                             : one && K <= 32 * kI2sBlockK && 2 * t <= cus;
-    if (gemv) return launch_i2s_decode(L, xq, x_scale, x_rowsum, M, K, stream, FMT);
-    if (t > 4 * cus) launch_wide<FMT>(L, xq, x_scale, x_rowsum, M, K, stream);
-    else if (shortk) launch_tile<1, 4, FMT>(L, xq, x_scale, x_rowsum, M, K, stream);
-    else if (t <= cus) launch_tile<1, 8, FMT>(L, xq, x_scale, x_rowsum, M, K, stream);
-    else if (t <= 2 * cus) launch_tile<2, 8, FMT>(L, xq, x_scale, x_rowsum, M, K, stream);
-    else launch_tile<2, 4, FMT>(L, xq, x_scale, x_rowsum, M, K, stream);
+    if (t > 4 * cus) return kTilesWide;
+    if (K <= 4 * kI2sBlockK) return kTiles32x4;
+    return t <= cus ? kTiles32x8 : t <= 2 * cus ? kTiles64x8 : kTiles64x4;
+}
+
+// Estimated times in us, each a line through what its kernel spends time on: the start, the chain of 256-k blocks, the
+// work groups on a CU, and their rounds.  Fitted to launches of 3000 shapes (17 to 112 tokens, K to 33024, 16 to 66048
+// rows, I2_S and TL1); one in six is off by more than 4 to 8%.
+double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K) {
+    const double cus = device_cus(), nkb = (double)((K + kI2sBlockK - 1) / kI2sBlockK);
+    const int rows = r == kTilesWide ? 128 : r == kTiles64x8 || r == kTiles64x4 ? 64 : 32;
+    int64_t groups = 0;
+    for (int i = 0; i < L.count; ++i) groups += (L.N[i] + rows - 1) / rows;
+    groups *= (M + kTok - 1) / kTok;
+    const double g = (double)groups / cus;                        // work groups a CU; the wide kernel keeps two resident
+    switch (r) {
+        case kTiles32x4: return 3.56 + 0.10 * nkb + 0.16 * g * nkb + 0.17 * g;
+        case kTiles32x8: return 3.65 + 0.14 * nkb + 0.03 * g * nkb + 0.52 * g;
+        case kTiles64x8: return 4.25 + 0.18 * nkb + 0.05 * g * nkb + 0.46 * g;
+        case kTiles64x4: return 4.50 + 0.34 * nkb + 0.04 * g * nkb + 0.59 * g;
+        default: return 7.06 + 0.06 * nkb + 0.16 * g * nkb + 0.30 * nkb * (double)((int64_t)(g / 2) + (2 * (int64_t)(g / 2) < g));
+    }
+}
+
+// The GEMV's token slices as launch_i2s_decode plans them; infinite where they are no candidate: up to four blocks of K
+// (the tiles were ahead in all but one of 200 shapes) and launches whose work groups walk more than three row groups, which
+// stream, and read every word once a slice (98 tokens, 2048 -> 6144 + 6144 rows: 22.8 against 17.6).
+double slices_us(const FusedLinears& L, int64_t M, int64_t K) {
+    const double never = __builtin_inf();
+    if (!i2s_sliced_ok(M, K, true) || K <= 4 * kI2sBlockK) return never;
+    const int64_t cus = device_cus(), nkb = (K + kI2sBlockK - 1) / kI2sBlockK;
+    const int64_t per = std::min<int64_t>(M, decode_slice_tokens(K)), slices = (M + per - 1) / per;
+    const bool four = nkb <= 16 && L.total > cus / 2;             // 4-wave groups, several to a CU; else 16 waves, one
+    const int64_t u = (nkb + (four ? 3 : 15)) / (four ? 4 : 16);  // blocks a wave
+    constexpr int64_t kByRegisters[4] = {5, 4, 3, 3}, kLds = 160 * 1024, kSums = 8192;
+    const int64_t occ = four ? std::max<int64_t>(1, std::min(kByRegisters[u - 1], kLds / (per * (K + 16) + kSums))) : 1;
+    int64_t gx = std::max<int64_t>(kNumXcd, cus * occ / slices / kNumXcd * kNumXcd);
+    const int64_t planned = (L.total + gx - 1) / gx;
+    gx = (L.total + planned - 1) / planned;
+    if (gx > kNumXcd) gx = gx / kNumXcd * kNumXcd;
+    const int64_t rounds = (L.total + gx - 1) / gx;               // row groups a work group walks
+    if (rounds > 3) return never;
+    const double fill = (double)(gx * slices) / (double)cus, staged = (double)(per * K) / 65536.0 * fill;
+    return four ? 3.87 - 0.15 * u + 0.19 * u * rounds + 0.11 * u * rounds * fill + 0.50 * staged
+                : 3.18 + 0.34 * u + 0.95 * rounds + 0.23 * u * rounds + 0.62 * staged;
+}
+
+// The GEMV's slices are the finer split (16 rows a work group, 16 waves on one row of blocks), the tiles the cheaper one per
+// word: few rows with long K go to the slices (us, slices / tiles: 64 rows of K = 11648 at 84 tokens 5.7 / 10.4; 512 of 10112
+// at 31 6.1 / 9.9; 3 x 1536 of 1536 at 112 6.8 / 7.6; 1152 of 3392 at 41 5.1 / 6.3), the rest to the tiles (4096 of 4096 at
+// 45 6.9 / 6.5; 4096 of 14336 at 45 20.0 / 12.0).  On a tie, the tiles.
+Route route_of(const FusedLinears& L, int64_t M, int64_t K) {
+    const Route r = tile_route(L, M, K);
+    return 1.02 * slices_us(L, M, K) < tiles_us(r, L, M, K) ? kGemvSlices : r;
+}
+
+template <int FMT>
+hipError_t launch_fmt(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum, int M,
+                      int K, hipStream_t stream) {
+    switch (route_of(L, M, K)) {
+        case kGemvSlices: return launch_i2s_decode(L, xq, x_scale, x_rowsum, M, K, stream, FMT);
+        case kTiles32x4: launch_tile<1, 4, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
+        case kTiles32x8: launch_tile<1, 8, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
+        case kTiles64x8: launch_tile<2, 8, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
+        case kTiles64x4: launch_tile<2, 4, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
+        default: launch_wide<FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
+    }
     return hipGetLastError();
 }
 
 }  // namespace
+
+int smallbatch_route(const FusedLinears& L, int64_t M, int64_t K) { return route_of(L, M, K); }
+
+double smallbatch_us(const FusedLinears& L, int64_t M, int64_t K) {
+    return std::min(tiles_us(tile_route(L, M, K), L, M, K), slices_us(L, M, K));
+}
 
 hipError_t launch_smallbatch(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
                              int M, int K, hipStream_t stream, int fmt) {

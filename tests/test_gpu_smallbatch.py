@@ -1,7 +1,7 @@
-"""GPU parity of the small-batch regime (17 to 112 tokens): the decode GEMV in token slices of up to 16 (8 or 12 where
-a slice's codes must fit in LDS), one launch for all slices, for I2_S and TL1 weights, against the oracle, through
-bitnet_mpgemm and bitnet_mpgemm_fused; and the boundaries of the regime (113 tokens, no token sums: the prefill
-GEMM)."""
+"""GPU parity of the small-batch regime (17 tokens up to the prefill GEMM's range) for I2_S and TL1 weights, against the
+oracle, through bitnet_mpgemm and bitnet_mpgemm_fused: the tile kernels, the decode GEMV in token slices of up to 16 (12, 8
+or 4 where a slice's codes must fit in LDS, one launch for all slices), and the boundaries of the regime (113 tokens, no
+token sums)."""
 import numpy as np
 import pytest
 import torch
@@ -10,6 +10,7 @@ import paper_2502_11880_amd as B
 from oracle import bitnet_oracle as O
 from paper_2502_11880_amd import inputs
 from tests import hip_runner as H
+from tests.test_routes_cpu import SLICES, _route
 
 pytestmark = pytest.mark.gpu
 
@@ -29,8 +30,8 @@ def _vs_oracle(layout, M, N, K, seed, rowsum=True):
     H.check_y(H.to_np(y), y_ref, acc_ref)
 
 
-# Slices of 16 (K <= 8176), 12 (K = 8640) and 8 (K = 14336); last slices of 1..15 tokens; 4-wave groups (K <= 4096,
-# many row groups) and 16-wave groups; a short last block (K = 320).
+# One shape of every size class.  The slices of the GEMV: (32, 4096, 4096), (64, 1024, 8640) and (100, 512, 14336); tiles of
+# 32 rows: 320 and 64 of K (4 waves), (48, 208, 3200) (8); of 64 rows: (112, 4096, 4096) and (24, 9600, 4096) (8).
 @pytest.mark.parametrize("layout", ["i2s", "tl1"])
 @pytest.mark.parametrize("M,N,K", [(17, 64, 320), (24, 9600, 4096), (32, 4096, 4096), (48, 208, 3200),
                                    (64, 1024, 8640), (100, 512, 14336), (112, 4096, 4096), (33, 16, 64)])
@@ -46,7 +47,28 @@ def test_small_batch_boundaries(layout, M, rowsum):
     _vs_oracle(layout, M, 256, 1536, seed=inputs.seed_for(14, 900 + M), rowsum=rowsum)
 
 
-# The 8B-class groups at 32 and 112 tokens through the fused call (quantiser + one sliced launch per group).
+# Every shape of the GEMV's token slices: 4-wave groups (more than 128 row groups, K <= 4096) with 2, 3 and 4 blocks a wave,
+# 16-wave groups with 1, 2, 3 and 4; slices of 16, 12 (K = 10112), 8 (12672 and 16128) and 4 (16384) tokens, the last one
+# full or of 1 to 15; short last blocks.
+@pytest.mark.parametrize("layout", ["i2s", "tl1"])
+@pytest.mark.parametrize("M,N,K", [(112, 4608, 1536), (17, 3072, 1536), (33, 2560, 2560), (17, 3456, 3456), (41, 1152, 3392),
+                                   (46, 1136, 7808), (31, 512, 10112), (26, 304, 12672), (65, 48, 16128), (109, 16, 16384)])
+def test_small_batch_token_slices(layout, M, N, K):
+    _announce("small batch token slices", layout, M, N, K)
+    assert _route(M, K, [N]) == SLICES
+    _vs_oracle(layout, M, N, K, seed=inputs.seed_for(14, 6000 + M + N + K))
+
+
+# Rows longer than the decode GEMV takes in slices (K > 16384), past 16 tokens: tiles of 32 and 64 rows, and TL1 with more
+# than 112 tokens.
+@pytest.mark.parametrize("layout", ["i2s", "tl1"])
+@pytest.mark.parametrize("M,N,K", [(40, 48, 16448), (129, 32, 33024), (70, 4240, 17088)])
+def test_small_batch_long_rows(layout, M, N, K):
+    _announce("small batch long rows", layout, M, N, K)
+    _vs_oracle(layout, M, N, K, seed=inputs.seed_for(14, 7000 + M + N + K))
+
+
+# The 8B-class groups at 32, 64 and 112 tokens through the fused call (the quantiser, then one launch per group).
 @pytest.mark.parametrize("layout", ["i2s", "tl1"])
 @pytest.mark.parametrize("M,K,Ns", [(32, 4096, [4096, 1024, 1024]), (112, 4096, [14336, 14336]),
                                     (64, 14336, [4096])])
@@ -59,7 +81,8 @@ def test_small_batch_fused(layout, M, K, Ns):
 # Every tile shape of the small-batch kernels at its edges (32-row x 32-token tiles t against 256 CUs): 32 rows with 4 and
 # 8 waves, 64 rows with 8 waves (256 < t <= 512) and 4 (to 1024), the wide kernel (past 1024; odd and even numbers of
 # 512-k stages); short last blocks of 1, 2 and 3 sub-tiles; row counts that end inside a tile; one token past a tile;
-# past 112 tokens the launches that leave the prefill GEMM, and TL1 at its last 256 tokens and one past (TL2 through its rewritten words).  Sums are exact integers.
+# past 112 tokens the launches that leave the prefill GEMM, and TL1 at its last 256 tokens and one past (TL2 through its
+# rewritten words).  Sums are exact integers.
 @pytest.mark.parametrize("layout", ["i2s", "tl1"])
 @pytest.mark.parametrize("M,N,K", [(65, 304, 704), (97, 48, 1088), (49, 4176, 2112), (112, 5136, 1152),
                                    (112, 8304, 1216), (65, 11024, 1088), (112, 10256, 192), (129, 208, 1344),
