@@ -187,8 +187,10 @@ hipError_t launch_quantize_act(const float* x, int64_t M, int64_t K, int8_t* xq,
                                int32_t* x_rowsum, hipStream_t stream) {
     // Few rows: wide groups so one row is spread over many lanes.  Many rows of up to 4096: one wave each;
     // longer rows: one 256-lane group each.
-    // (a row of up to 8192 by 512 lanes: 2.57 us against 2.72 for 8 rows of 4096; the same from 14336 on)
-    if (M <= 64 && K <= 8192) return launch_block<512>(x, M, K, xq, x_scale, x_rowsum, stream);
+    // (a row of up to 8192 by 512 lanes: 2.57 us against 2.72 for 8 rows of 4096; the same from 14336 on.  Rows that are
+    // not whole float4s, read one float at a time, stay with 1024: 16 rows of 7158 4.6 us against 5.9, of 1025 3.2 against
+    // 3.3)
+    if (M <= 64 && K <= 8192 && K % 4 == 0) return launch_block<512>(x, M, K, xq, x_scale, x_rowsum, stream);
     if (M <= 64) return launch_block<1024>(x, M, K, xq, x_scale, x_rowsum, stream);
     if (K % 4 == 0 && K <= 1024) return launch_wave<4>(x, M, K, xq, x_scale, x_rowsum, stream);
     if (K % 4 == 0 && K <= 2048) return launch_wave<8>(x, M, K, xq, x_scale, x_rowsum, stream);

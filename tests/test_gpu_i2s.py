@@ -22,7 +22,7 @@ def _announce(*what):
 # a3: activation quantisation
 # ------------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("M,K", [(1, 64), (1, 1536), (3, 1001), (8, 4096), (17, 3200), (1, 33024), (96, 14336),
-                                 (2, 1)])
+                                 (2, 1), (64, 7158), (16, 8191), (5, 8192), (5, 8193)])
 def test_quantize_act_bit_exact(M, K):
     _announce("quantize", M, K)
     x = inputs.activation_f32(M, K, seed=inputs.seed_for(9, M * 7 + K))
