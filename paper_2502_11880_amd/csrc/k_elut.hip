@@ -471,9 +471,10 @@ hipError_t launch_fmt(const FusedLinears& L, const float* x, const int8_t* xq, c
     const int64_t fit = (int64_t)(kElutLds / (size_t)(nkb * T::BK + 16));
     const int slice = fit < 16 ? (int)fit : 16;
     // 4-wave groups where a row fits one batch of theirs and there are row groups for half the CUs: several groups per
-    // CU do not wait on one another's barriers.  Otherwise 16 waves, the batches of a row group balanced (up to two
-    // blocks per wave: with more the kernel spills).  Rows of K > 122000 leave LDS only for the partial sums of 8 waves.
-    if (nkb <= 16 && L.total > device_cus() / 2) {
+    // CU do not wait on one another's barriers; and where a row has no work for a fifth wave (1024 rows of K = 960 at
+    // one token: C4G2 5.6 us with 16 waves, 4.6 with 4; C3G5 5.9 and 4.8).  Otherwise 16 waves, the batches of a row group
+    // balanced (up to two blocks per wave: with more the kernel spills).  Rows of K > 122000 leave LDS only for the partial sums of 8 waves.
+    if (nkb <= 4 || (nkb <= 16 && L.total > device_cus() / 2)) {
         const int u = (nkb + 3) / 4;
         if (u <= 1) return launch_cfg<F, 4, 1>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
         if (u <= 2) return launch_cfg<F, 4, 2>(L, x, xq, x_scale, M, K, slice, xq_out, s_out, rs_out, s);
