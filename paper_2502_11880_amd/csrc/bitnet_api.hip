@@ -117,9 +117,24 @@ bool tl2_via_i2s(int64_t M, int64_t N, int64_t K) {
 
 // TL2_0 / TL1_0 with the codes given: one and two tokens by table lookups, more as one-hot products on MFMA, up to 16
 // tokens a slice.  (Two tokens: one 100B-class layer takes 351 us by TL2_0 lookups and 439 as products, TL1_0 471 and 594;
-// from three on the products win everywhere, the 1B-class layers 55 -> 46 us, the 3B-class ones at four 94 -> 70.)
+// from three on the products win, the 1B-class layers 55 -> 46 us, the 3B-class ones at four 94 -> 70.)  Three tokens of
+// TL1_0 with K > 16384 and two to three row groups a CU are a lookup of two and one of one: the lookups' one work group a
+// row group fills its last round there, and the products' two row groups a work group leave the second round half empty
+// (us, products / lookups: 33024 -> 12288 162 / 144, 17024 -> 8224 82 / 77; past three a CU 33024 -> 14336 166 / 179, up to
+// two 33024 -> 4096 49 / 55).
 hipError_t lossy_run(bool tl1, const bitnet::FusedLinears& L, const int8_t* xq, const float* x_scale, int64_t M, int64_t K,
                      hipStream_t s) {
+    const int64_t cus = bitnet::device_cus();
+    if (tl1 && M == 3 && K > 16384 && L.total > 2 * cus && L.total <= 3 * cus) {
+        const hipError_t e = lossy_run(true, L, xq, x_scale, 2, K, s);
+        if (e != hipSuccess) return e;
+        bitnet::FusedLinears third = L;
+        for (int i = 0; i < L.count; ++i) {
+            third.y[i] = L.y[i] + 2 * (int64_t)L.N[i];
+            third.acc[i] = L.acc[i] ? L.acc[i] + 2 * (int64_t)L.N[i] : nullptr;
+        }
+        return lossy_run(true, third, xq + 2 * K, x_scale + 2, 1, K, s);
+    }
     if (M > 2) return bitnet::launch_lossy(tl1, L, xq, x_scale, M, (int)K, s);
     return tl1 ? bitnet::launch_tl1_elut_decode(L, nullptr, xq, x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s)
                : bitnet::launch_tl2_elut_decode(L, nullptr, xq, x_scale, (int)M, (int)K, nullptr, nullptr, nullptr, s, true);

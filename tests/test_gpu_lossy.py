@@ -115,3 +115,13 @@ def test_lossy_edges(layout, M, N, K):
     acc_ref = gemm_ref(xq_np, pack_ref(t_ref), N, K)
     assert np.array_equal(H.to_np(acc), acc_ref)
     H.check_y(H.to_np(y), O.epilogue(acc_ref, beta, s_np), acc_ref)
+
+
+# Three tokens of TL1_0 on long rows: two and one by lookups from more than two row groups a CU to three (512 and 768 of
+# 256 CUs), one-hot products on both sides of that; one weight and several.
+@pytest.mark.parametrize("K,Ns", [(16448, [8224]), (16448, [8176, 32, 16]), (16448, [12288]), (16448, [8192]),
+                                  (16448, [12304]), (16384, [8224])])
+def test_tl1_0_three_tokens_long_rows(K, Ns):
+    _announce("TL1_0, three tokens", K, Ns)
+    from tests.test_gpu_fused import _fused_case_lossy
+    _fused_case_lossy("tl1_0", 3, K, Ns, sample_groups=1)
