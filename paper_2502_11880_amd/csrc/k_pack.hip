@@ -166,9 +166,10 @@ __global__ __launch_bounds__(kMeanThreads) void absmean_kernel(const float4* __r
     drain();
     __syncthreads();
     // The first wave adds this group's buckets to the device's; bucket 0 counts the groups that are done, and the last
-    // one makes beta.  Everything handed over is an agent-scope atomic, so the count only has to follow the adds: it is
-    // issued once the adds have returned their old values.  (A release fence here writes back the XCD's whole L2: the
-    // fences of 512 groups took 100 us.)
+    // one makes beta.  Everything handed over is an agent-scope atomic, so the count only has to follow the adds: the wave
+    // waits until they have returned their old values (the memory clobber keeps the compiler from moving the count up).
+    // That orders them on this chip; the memory model would want a release here, which writes back the XCD's whole L2: the
+    // fences of 512 groups took 100 us.
     if (tid < 64) {
 #pragma unroll
         for (int g = 0; g < kBuckets / 64; ++g) {
@@ -176,8 +177,9 @@ __global__ __launch_bounds__(kMeanThreads) void absmean_kernel(const float4* __r
             const unsigned long long s = b ? sb[b] : 0ull;
             unsigned long long old = s;
             if (s) old = __hip_atomic_fetch_add(&buckets[b], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            asm volatile("" : "+v"(old) : : "memory");   // waits for the returned value
+            asm volatile("" : "+v"(old) : : "memory");   // the form that returns the value
         }
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         if (tid == 0)
             last_s = __hip_atomic_fetch_add(&buckets[0], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                      (unsigned long long)gridDim.x - 1;
