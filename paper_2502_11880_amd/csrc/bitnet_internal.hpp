@@ -28,12 +28,6 @@ __device__ __forceinline__ int xcd_logical_id(int bid, int nblocks) {
     return xcd * per + (xcd < extra ? xcd : extra) + idx;
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
-}
-
 // Reductions over the 64 lanes of a wave, the result in every lane: DPP steps inside each row of 16 lanes
 // (swap neighbours, swap pairs, rotate the row by 4 and by 8), then the four row results read as scalars.
 __device__ __forceinline__ int dpp_row_step(int v, int ctrl_sel) {

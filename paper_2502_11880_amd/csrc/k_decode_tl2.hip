@@ -341,10 +341,10 @@ __global__ __launch_bounds__(64 * WAVES) void tl2_elut_decode_kernel(
 }
 
 // One or two tokens of TL1_0 by table lookup (Algorithm TL1; Table 5; Sec. 3.2.1; one token where the row's tables do not
-// fit in LDS), one work group per 16-row group: wave w takes the 256-k blocks w, w + WAVES, ... (four 64-k units each, the last block
-// possibly fewer); lane l builds the 9-entry tables of pair l % 32 of units l / 32 and 2 + l / 32, quantised to int8 with
-// the unit's power-of-two scale, and lane (r, q) looks up the 8 pairs of each of its block's words (row r, k = 64 j +
-// 16 q .. + 15 of unit j); the unit's sum is scaled back.  Fused weight groups and QX as for the TL2 kernel.
+// fit in LDS), one work group per 16-row group: wave w takes the 256-k blocks w, w + WAVES, ... (four 64-k units each, the
+// last block possibly fewer); lane l builds the 9-entry tables of pair l % 32 of units l / 32 and 2 + l / 32, quantised to
+// int8 with the unit's power-of-two scale, and lane (r, q) looks up the 8 pairs of each of its block's words (row r, k =
+// 64 j + 16 q .. + 15 of unit j); the unit's sum is scaled back.  Fused weight groups and QX as for the TL2 kernel.
 constexpr int kTl1BlockStride = 128 * kSlot;                 // the 128 pair tables of a 256-k block
 
 // Largest value of each half-wave (lanes 0..31 and 32..63) of v, as scalars: DPP maxima inside each row of 16 lanes,
@@ -364,7 +364,6 @@ __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
     __shared__ float redf[WAVES];
     __shared__ int redi[WAVES];
     static_assert(!QX || MT == 1, "the fused quantiser takes one token");
-    constexpr int TC = tl2_elut_chunk(MT);      // tokens whose tables share LDS at a time
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int q = lane >> 4, r = lane & 15;
     const int pr = lane & 31, hh = lane >> 5;  // this lane builds pair pr of units hh and 2 + hh
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
     const int nsub = K / kSubK;
     const int nkb = (nsub + 3) / 4;
     const uint8_t* rgbase = packed + (size_t)rg * 4 * K;
-    uint8_t* lut = lds + (size_t)wave * TC * kTl1BlockStride;
+    uint8_t* lut = lds + (size_t)wave * MT * kTl1BlockStride;
 
     int acc[MT];
 #pragma unroll
@@ -393,93 +392,87 @@ __global__ __launch_bounds__(64 * WAVES) void tl1_elut_decode_kernel(
             word[j] = *reinterpret_cast<const uint32_t*>(rgbase + (size_t)sb * 1024 + 4 * T * lane + 4 * min(j, T - 1));
         const bool ok0 = hh < T, ok1 = 2 + hh < T;
         const int u0 = min(hh, T - 1), u1 = min(2 + hh, T - 1);
+        int sh[MT][4];
 #pragma unroll
-        for (int c = 0; c < MT; c += TC) {
-            if (c >= M) break;
-            int sh[TC][4];
+        for (int jj = 0; jj < MT; ++jj)
 #pragma unroll
-            for (int jj = 0; jj < TC; ++jj)
+            for (int j = 0; j < 4; ++j) sh[jj][j] = 0;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) sh[jj][j] = 0;
-#pragma unroll
-            for (int jj = 0; jj < TC; ++jj) {
-                const int m = c + jj;
-                if (m >= M) break;
-                const size_t kb0 = (size_t)sb * kI2sBlockK + 2 * pr;
-                int a0, a1, b0, b1;
-                if constexpr (QX) {
-                    a0 = code_of(x[kb0 + kSubK * u0], sx);
-                    a1 = code_of(x[kb0 + kSubK * u0 + 1], sx);
-                    b0 = code_of(x[kb0 + kSubK * u1], sx);
-                    b1 = code_of(x[kb0 + kSubK * u1 + 1], sx);
-                    if (qw) {
-                        if (ok0) {
-                            xq_out[kb0 + kSubK * u0] = (int8_t)a0;
-                            xq_out[kb0 + kSubK * u0 + 1] = (int8_t)a1;
-                            csum += a0 + a1;
-                        }
-                        if (ok1) {
-                            xq_out[kb0 + kSubK * u1] = (int8_t)b0;
-                            xq_out[kb0 + kSubK * u1 + 1] = (int8_t)b1;
-                            csum += b0 + b1;
-                        }
+        for (int jj = 0; jj < MT; ++jj) {
+            if (jj >= M) break;
+            const size_t kb0 = (size_t)sb * kI2sBlockK + 2 * pr;
+            int a0, a1, b0, b1;
+            if constexpr (QX) {
+                a0 = code_of(x[kb0 + kSubK * u0], sx);
+                a1 = code_of(x[kb0 + kSubK * u0 + 1], sx);
+                b0 = code_of(x[kb0 + kSubK * u1], sx);
+                b1 = code_of(x[kb0 + kSubK * u1 + 1], sx);
+                if (qw) {
+                    if (ok0) {
+                        xq_out[kb0 + kSubK * u0] = (int8_t)a0;
+                        xq_out[kb0 + kSubK * u0 + 1] = (int8_t)a1;
+                        csum += a0 + a1;
                     }
-                } else {
-                    const int8_t* xb = xq + (size_t)m * K + kb0;
-                    a0 = xb[kSubK * u0];
-                    a1 = xb[kSubK * u0 + 1];
-                    b0 = xb[kSubK * u1];
-                    b1 = xb[kSubK * u1 + 1];
+                    if (ok1) {
+                        xq_out[kb0 + kSubK * u1] = (int8_t)b0;
+                        xq_out[kb0 + kSubK * u1 + 1] = (int8_t)b1;
+                        csum += b0 + b1;
+                    }
                 }
-                {
-                    int lo0, hi0, lo1, hi1;
-                    half_wave_max(ok0 ? abs(a0) + abs(a1) : 0, lo0, hi0);
-                    half_wave_max(ok1 ? abs(b0) + abs(b1) : 0, lo1, hi1);
-                    sh[jj][0] = lossy_shift_of(lo0);
-                    sh[jj][1] = lossy_shift_of(hi0);
-                    sh[jj][2] = lossy_shift_of(lo1);
-                    sh[jj][3] = lossy_shift_of(hi1);
-                }
-                uint32_t w[8];
-                uint8_t* tj = lut + jj * kTl1BlockStride;
-                if (ok0) {
-                    pair_table(a0, a1, w);
-                    quantize_words(w, hh ? sh[jj][1] : sh[jj][0]);
-                    store_table(tj + (32 * hh + pr) * kSlot, w);
-                }
-                if (ok1) {
-                    pair_table(b0, b1, w);
-                    quantize_words(w, hh ? sh[jj][3] : sh[jj][2]);
-                    store_table(tj + (64 + 32 * hh + pr) * kSlot, w);
-                }
+            } else {
+                const int8_t* xb = xq + (size_t)jj * K + kb0;
+                a0 = xb[kSubK * u0];
+                a1 = xb[kSubK * u0 + 1];
+                b0 = xb[kSubK * u1];
+                b1 = xb[kSubK * u1 + 1];
             }
-            wave_lds_handoff();
-            // lookups: tokens past M read the chunk's first tables and are never stored
-            int usum[TC][4];
-#pragma unroll
-            for (int jj = 0; jj < TC; ++jj)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) usum[jj][j] = 0;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (j >= T) break;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    // pair i of the word: byte i % 4, low nibble for i < 4; it is pair 8 q + i of unit j
-                    const int code = (int)((word[j] >> (8 * (i & 3) + 4 * (i >> 2))) & 15u);
-                    const uint8_t* e = lut + (32 * j + 8 * q + i) * kSlot + 2 * code;
-#pragma unroll
-                    for (int jj = 0; jj < TC; ++jj)
-                        usum[jj][j] += lds_i16(e + (c + jj < M ? jj : 0) * kTl1BlockStride);
-                }
+            {
+                int lo0, hi0, lo1, hi1;
+                half_wave_max(ok0 ? abs(a0) + abs(a1) : 0, lo0, hi0);
+                half_wave_max(ok1 ? abs(b0) + abs(b1) : 0, lo1, hi1);
+                sh[jj][0] = lossy_shift_of(lo0);
+                sh[jj][1] = lossy_shift_of(hi0);
+                sh[jj][2] = lossy_shift_of(lo1);
+                sh[jj][3] = lossy_shift_of(hi1);
             }
-#pragma unroll
-            for (int jj = 0; jj < TC; ++jj)
-                if (c + jj < MT)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[c + jj] += usum[jj][j] << sh[jj][j];
-            wave_lds_handoff();
+            uint32_t w[8];
+            uint8_t* tj = lut + jj * kTl1BlockStride;
+            if (ok0) {
+                pair_table(a0, a1, w);
+                quantize_words(w, hh ? sh[jj][1] : sh[jj][0]);
+                store_table(tj + (32 * hh + pr) * kSlot, w);
+            }
+            if (ok1) {
+                pair_table(b0, b1, w);
+                quantize_words(w, hh ? sh[jj][3] : sh[jj][2]);
+                store_table(tj + (64 + 32 * hh + pr) * kSlot, w);
+            }
         }
+        wave_lds_handoff();
+        // lookups: a token past M reads the first one's tables and is never stored
+        int usum[MT][4];
+#pragma unroll
+        for (int jj = 0; jj < MT; ++jj)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) usum[jj][j] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j >= T) break;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                // pair i of the word: byte i % 4, low nibble for i < 4; it is pair 8 q + i of unit j
+                const int code = (int)((word[j] >> (8 * (i & 3) + 4 * (i >> 2))) & 15u);
+                const uint8_t* e = lut + (32 * j + 8 * q + i) * kSlot + 2 * code;
+#pragma unroll
+                for (int jj = 0; jj < MT; ++jj)
+                    usum[jj][j] += lds_i16(e + (jj < M ? jj : 0) * kTl1BlockStride);
+            }
+        }
+#pragma unroll
+        for (int jj = 0; jj < MT; ++jj)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[jj] += usum[jj][j] << sh[jj][j];
+        wave_lds_handoff();
     }
 
     // Reduce: over the four q quarters (lanes r, r+16, r+32, r+48), then over waves.

@@ -162,7 +162,8 @@ __device__ __forceinline__ void load_words(uint32_t (&c)[A], const int8_t* src) 
 // TL1: the packed words are TL1's (TL1_0), else TL2's (TL2_0).  At most 16 / DUP tokens (DUP 1, 2 or 4): the lanes r,
 // r + 16 / DUP, ... of a quarter hold the same token and build a share of its tables each.
 template <bool TL1, int DUP, int WAVES, int RG>
-__global__ __attribute__((amdgpu_waves_per_eu(TL1 ? (RG <= 4 ? 4 : 2) : RG == 1 && DUP > 1 ? 4 : 2, 4))) __launch_bounds__(64 * WAVES) void lossy_kernel(
+__global__ __attribute__((amdgpu_waves_per_eu(TL1 ? (RG <= 4 ? 4 : 2) : RG == 1 && DUP > 1 ? 4 : 2, 4)))
+__launch_bounds__(64 * WAVES) void lossy_kernel(
     FusedLinears L, const int8_t* __restrict__ xq, const float* __restrict__ x_scale, int M, int K, int slice) {
     __shared__ v4i red[WAVES][RG][64];
 
@@ -362,8 +363,8 @@ void launch_cfg(const FusedLinears& L, const int8_t* xq, const float* x_scale, i
 }
 
 // Few row groups: 16 waves share one (the block loop is the longest chain), then 8 in two groups per CU.  Else 4-wave
-// groups, two per CU (TL1, which has 8 tables at a time: four), with as few row groups each as keep the launch within one round, so that the tables are
-// built as seldom as the grid allows.  (Nine tokens and more keep all of their tables in one lane each: 8 waves and 4
+// groups, two per CU (TL1, which has 8 tables at a time: four), with as few row groups each as keep the launch within one
+// round, so that the tables are built as seldom as the grid allows.  (Nine tokens and more keep all of their tables in one lane each: 8 waves and 4
 // row groups are what their registers allow.)
 template <bool TL1, int DUP>
 void launch_rg(const FusedLinears& L, const int8_t* xq, const float* x_scale, int M, int K, int slice, hipStream_t s) {
