@@ -559,10 +559,10 @@ bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* 
         via = via && tl2_via_i2s(M, N[i], K);
         words += align256((size_t)N[i] * (size_t)K / 4);
     }
+    if (via && !tl2 && bitnet::smallbatch_beats_prefill(L, M, K, true))       // reads TL1 words: nothing to rewrite
+        return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
+                          "bitnet_mpgemm_fused launch");
     if (via && ws_bytes >= words) {
-        if (!tl2 && bitnet::smallbatch_beats_prefill(L, M, K, true))          // reads TL1 words: nothing to rewrite
-            return hip_status(bitnet::launch_smallbatch(L, xq, x_scale, x_rowsum, (int)M, (int)K, s, bitnet::kFmtTl1),
-                              "bitnet_mpgemm_fused launch");
         bitnet::FusedLinears T = L;
         size_t off = 0;
         void* dst[bitnet::kMaxFused];

@@ -92,13 +92,15 @@ def test_small_batch_shapes(layout, M, N, K):
     _vs_oracle(layout, M, N, K, seed=inputs.seed_for(14, 3000 + M + N + K))
 
 
+# With the workspace of the largest weight (less than TL1's rewritten words of all of them) and with the whole one.
+@pytest.mark.parametrize("split_ws", [False, True], ids=["one weight's workspace", "the group's workspace"])
 @pytest.mark.parametrize("layout", ["i2s", "tl1", "tl2"])
 @pytest.mark.parametrize("M,K,Ns", [(40, 1536, [1040, 272, 16]), (113, 4096, [4096, 1024, 1024]),
                                     (200, 1152, [3472, 3456])])
-def test_small_batch_fused_shapes(layout, M, K, Ns):
-    _announce("small batch fused shape", layout, M, K, Ns)
+def test_small_batch_fused_shapes(layout, M, K, Ns, split_ws):
+    _announce("small batch fused shape", layout, M, K, Ns, split_ws)
     from tests.test_gpu_fused import _fused_case
-    _fused_case(layout, M, K, Ns, seed=inputs.seed_for(14, 4000 + M + K + len(Ns)))
+    _fused_case(layout, M, K, Ns, seed=inputs.seed_for(14, 4000 + M + K + len(Ns)), split_ws=split_ws)
 
 
 # 2^28 rows at 112 tokens: 2^32 threads of the wide kernel in one launch would be one too many, so the tokens go in two.
