@@ -1,6 +1,6 @@
 """GPU parity of the integer-weight ELUT layouts (Appendix "Insight", Table 3, Algorithm "ELUT mpGEMM"): packing
-bit-exact against the oracle's formats, and the table-lookup accumulation and epilogue against the oracle's MAD sum,
-for C = 4 and C = 5 with g = 2 and ternary groups of g = 5."""
+bit-exact against the oracle's formats, and the accumulation and epilogue against the oracle's MAD sum, for C = 4 and
+C = 5 with g = 2 and ternary groups of g = 5."""
 import numpy as np
 import pytest
 import torch
@@ -66,9 +66,8 @@ def _vs_oracle(fmt, M, N, K, seed, extreme=False):
     return acc_ref
 
 
-# 1 to 17 tokens (slices of 4, or 2 for c3g5), partial last blocks (K = 640, 3200, 8640), the 3B-class shapes, and
-# every rows-per-wave count the launcher picks (1 to 8: the fewest rows per wave that keep one work group per CU;
-# N = 12288 .. 30720 take 3, 4, 5, 6, 7 and 8 on 256 CUs).
+# 1 to 17 tokens (one and two token slices), partial last blocks (K = 640, 3200, 8640), the 3B-class shapes, and many row
+# groups for each work group (N = 12288 .. 30720 on 256 CUs).
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("M,N,K", [(1, 16, 640), (2, 48, 1280), (3, 208, 3200), (5, 64, 8640), (8, 3200, 3200),
                                    (17, 96, 640), (1, 9600, 640), (1, 8640, 3200), (3, 12288, 640), (1, 16384, 640),
@@ -109,8 +108,8 @@ def test_elut_fused_and_noalloc(fmt):
         assert np.array_equal(H.to_np(y2), H.to_np(y))
 
 
-# The fused call: every weight of the group in one table-lookup launch (rows of several weights in one work group,
-# ragged row counts); at one token the launch also quantises the row (codes, scale and code sum bit-exact against
+# The fused call: every weight of the group in one launch (rows of several weights in one work group, ragged row
+# counts); at one token the launch also quantises the row (codes, scale and code sum bit-exact against
 # the oracle's quantiser), otherwise the quantiser runs first.  Outputs against the oracle and bit-identical to the
 # separate calls.
 @pytest.mark.parametrize("fmt", FMTS)
@@ -160,16 +159,20 @@ def test_elut_fused_workload_groups(fmt, M, K, Ns):
     _elut_fused(fmt, M, K, Ns)
 
 
-# Where the MFMA form can go wrong: rows of less than one block, ragged last blocks, one row group, several batches of
-# a row group (K > 8192), token slices (more than 16 tokens, or as many as fit in LDS: 3 at K = 33024, 1 past 61000),
-# the 8-wave rows past 122000, with codes of both signs at their largest.
+# Where the MFMA form can go wrong: rows of less than one block, ragged last blocks, one row group, rows of one batch on
+# 4-wave groups (up to four blocks of few rows, up to 16 of many), several batches of a row group (K > 8192), token slices
+# (more than 16 tokens, or as many as fit in LDS: 3 at K = 33024, 1 past 61000), the 8-wave rows past 122000; with ordinary
+# weights and codes, and with both at their largest in both signs, where the offsets that the epilogue subtracts are too.
+@pytest.mark.parametrize("extreme", [False, True], ids=["", "extreme"])
 @pytest.mark.parametrize("fmt", FMTS)
 @pytest.mark.parametrize("M,N,K", [(1, 16, 64), (5, 48, 192), (16, 16, 448), (17, 2080, 320), (33, 64, 4160),
                                    (9, 48, 8512), (1, 4112, 4096), (8, 32, 33024), (2, 32, 61504), (1, 16, 132096),
-                                   (3, 32, 132096), (2, 4128, 960)])
-def test_elut_edges(fmt, M, N, K):
+                                   (3, 32, 132096), (2, 4128, 960), (1, 1024, 960),
+                                   (3, 48, 1024), (2, 48, 1088)])
+def test_elut_edges(fmt, M, N, K, extreme):
     if fmt == "c3g5":
         K = max(320, K // 320 * 320)
-    _announce("elut edges", fmt, M, N, K)
-    _vs_oracle(fmt, M, N, K, seed=inputs.seed_for(13, 700 + M * 31 + N + K))
-    _elut_fused(fmt, M, K, [N, 16])
+    _announce("elut edges", fmt, M, N, K, "extreme" if extreme else "")
+    _vs_oracle(fmt, M, N, K, seed=inputs.seed_for(13, 700 + M * 31 + N + K), extreme=extreme)
+    if not extreme:
+        _elut_fused(fmt, M, K, [N, 16])

@@ -192,8 +192,8 @@ def test_fused_one_token_100b_groups(K, Ns):
 
 
 def _fused_case_lossy(layout, M=3, K=1600, Ns=(64, 208), sample_groups=None):
-    """bitnet_mpgemm_fused on a lossy layout: one table-lookup launch per slice of up to 8 tokens over every weight
-    (one token quantised inside it, else the quantiser first); the codes, scales and sums bit-exact, the outputs
+    """bitnet_mpgemm_fused on a lossy layout: one launch over every weight, table lookups for one and two tokens and
+    one-hot products past that (one token quantised inside it, else the quantiser first); the codes, scales and sums bit-exact, the outputs
     equal to the separate calls and to the oracle's lossy route.  sample_groups: the oracle route runs on the first,
     the last and that many seeded random 16-row groups of each weight (rows are independent in the packing and in
     the route, so packing only those rows gives their exact values); the separate calls are compared everywhere."""

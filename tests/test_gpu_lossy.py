@@ -1,5 +1,5 @@
 """GPU parity of the lossy TL2_0 and TL1_0 kernels (Table 1; Sec. 3.2.1): table lookups on tables quantised to int8
-with a power-of-two scale per token and table block.  The accumulators are the oracle's lossy integers exactly and
+with a power-of-two scale per token and table block (from three tokens on as one-hot products of the same tables).  The accumulators are the oracle's lossy integers exactly and
 the outputs within 1e-5 of their float64 epilogue; with codes small enough for every table entry to fit int8 they
 are the exact MAD sums."""
 import numpy as np
@@ -81,7 +81,7 @@ def test_lossy_fused_100b_groups(layout, K, Ns):
 
 
 # The 8B-class layer groups at one and eight tokens, as the benchmark runs them on the lossy layouts (one token: the
-# persistent kernels; eight: the quantiser, then the lookup kernels); the oracle's lossy route on sampled row groups.
+# persistent kernels; eight: the quantiser, then the one-hot products); the oracle's lossy route on sampled row groups.
 @pytest.mark.parametrize("layout", ["tl2_0", "tl1_0"])
 @pytest.mark.parametrize("M", [1, 8])
 @pytest.mark.parametrize("K,Ns", [(4096, (4096, 1024, 1024)), (4096, (4096,)), (4096, (14336, 14336)),
