@@ -6,9 +6,9 @@ turn; the layers hold copies of one packed layer in separate HBM buffers, so eve
 activation per token (int8, absmax) and multiplies it by the group's packed ternary weights with the fused
 dequantisation epilogue.  Each group is one bitnet_mpgemm_fused call: at one token a single launch that also
 quantises; otherwise the quantiser, then one launch for all the group's weights (the decode GEMV for M <= 16,
-the MFMA GEMM over the weights' concatenated row tiles for M > 16).  Decode also times the separate-call path
-(bitnet_quantize_act + one bitnet_mpgemm per weight) and reports it beside the value; prefill times the fused
-GEMM launches alone (on the already quantised activations) for its roofline.  Weights are ternarised and packed
+past that the small-batch kernels or the MFMA GEMM over the weights' concatenated row tiles).  Decode also times the
+separate-call path (bitnet_quantize_act + one bitnet_mpgemm per weight) and reports it beside the value; prefill
+times the fused GEMM launches alone (on the already quantised activations) for its roofline.  Weights are ternarised and packed
 once before timing (offline preprocessing); packed copies rotate so every step streams its weights from HBM
 rather than from the 256 MB Infinity Cache.
 
@@ -37,7 +37,7 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, GB/s
 INT8_PEAK_TOPS = 5000.0          # MI355X dense int8 MFMA, TOP/s
 ROT_BYTES = 512 << 20            # rotate through at least 2x the Infinity Cache
 DECODE_MAX_TOKENS = 16
-SMALL_BATCH_MAX = 112            # 17..112 tokens: the decode GEMV in token slices (I2_S, TL1)
+SMALL_BATCH_MAX = 112            # 17..112 tokens: the small-batch kernels (I2_S, TL1)
 CPU_ROWS = 512                   # oracle timing sample per weight for stacks of layers
 PARITY_EXIT = 3                  # exit status of a run whose figures stand beside a failed parity check
 METRIC = "decode GEMV weight GB/s (% HBM peak) + tokens/s; prefill int8 TOPS (% MFMA peak)"
@@ -71,7 +71,9 @@ def log(msg):
     print(f"[bench {time.strftime('%H:%M:%S')}] {msg}", file=sys.stderr, flush=True)
 
 
-LOSSY = {"tl2_0": "tl2_elut_decode_kernel", "tl1_0": "tl1_elut_decode_kernel"}   # layout -> kernel
+LOSSY = {"tl2_0": ("tl2_stream_kernel", "tl2_elut_decode_kernel"),    # layout -> one token (K up to 14336), few tokens
+         "tl1_0": ("tl1_lossy_stream_kernel", "tl1_elut_decode_kernel")}
+SMALL_KERNELS = "smallbatch_kernel, smallbatch_wide_kernel or i2s_decode_stream_kernel in token slices"
 INT_BETA = 0.02                  # per-tensor scale given with the integer-weight layouts' weights
 INT_C = {"c4g2": 4, "c5g2": 5, "c3g5": 3}
 
@@ -285,9 +287,14 @@ def main():
         achieved = avg_bytes / (avg_launch_ms * 1e-3) / 1e9
         words = " on TL1 words" if layout == "tl1" else ""
         if int_layout(layout):
-            kernel = f"elut_generic_kernel ({layout} table lookups) per weight, after quantize_rows_reg per group"
+            kernel = (f"elut_kernel ({layout}, one token: quantiser fused)" if M == 1 else
+                      f"elut_kernel ({layout}) per group, after quantize_rows_reg")
         elif layout in LOSSY:
-            kernel = f"{LOSSY[layout]} (int8-quantised tables) per weight, after quantize_rows_reg per group"
+            stream, few = LOSSY[layout]
+            kernel = (f"{stream} (int8-quantised tables, one token: quantiser fused; {few} past K = 14336)"
+                      if M == 1 else
+                      f"{few} (int8-quantised tables) per group, after quantize_rows_reg" if M == 2 else
+                      f"lossy_kernel ({layout}: one-hot products) per group, after quantize_rows_reg")
         elif layout == "tl2" and M == 1:
             kernel = "tl2_mfma_decode_kernel (bitnet_mpgemm_fused, one token: quantiser fused)"
         elif layout == "tl2":
@@ -309,14 +316,15 @@ def main():
         avg_launch_ms = second_ms / launches
         sliced = M <= SMALL_BATCH_MAX and layout in ("i2s", "tl1")
         if sliced:
-            kernel = (f"i2s_decode_stream_kernel{' on TL1 words' if layout == 'tl1' else ''} in token slices "
+            kernel = (f"{SMALL_KERNELS}{' on TL1 words' if layout == 'tl1' else ''} "
                       "(bitnet_mpgemm_fused, 17-112 tokens: one launch per activation group)")
         elif int_layout(layout):
-            kernel = f"elut_generic_kernel ({layout} table lookups) per weight"
+            kernel = f"elut_kernel ({layout}) in 16-token slices, one launch per activation group"
         elif layout in LOSSY:
-            kernel = f"{LOSSY[layout]} (int8-quantised tables) in 8-token slices per weight"
+            kernel = f"lossy_kernel ({layout}: one-hot products) in 16-token slices, one launch per activation group"
         else:
-            kernel = "i2s_prefill_kernel (bitnet_mpgemm_fused, M > 16: one launch per activation group)"
+            kernel = ("i2s_prefill_kernel, or the small-batch kernels where it would split K (bitnet_mpgemm_fused, "
+                      "M > 16: one launch per activation group)")
             if layout != "i2s":
                 kernel = f"{layout}_to_i2s transcoding per group + " + kernel
         # the roofline that binds: HBM for the weight stream (packed weights, the codes read, the fp32 outputs
