@@ -290,8 +290,8 @@ def main():
             kernel = (f"elut_kernel ({layout}, one token: quantiser fused)" if M == 1 else
                       f"elut_kernel ({layout}) per group, after quantize_rows_reg")
         elif layout in LOSSY:
-            stream, few = LOSSY[layout]
-            kernel = (f"{stream} (int8-quantised tables, one token: quantiser fused; {few} past K = 14336)"
+            persistent, few = LOSSY[layout]
+            kernel = (f"{persistent} (int8-quantised tables, one token: quantiser fused; {few} past K = 14336)"
                       if M == 1 else
                       f"{few} (int8-quantised tables) per group, after quantize_rows_reg" if M == 2 else
                       f"lossy_kernel ({layout}: one-hot products) per group, after quantize_rows_reg")
