@@ -240,8 +240,8 @@ hipError_t launch_smallbatch(const FusedLinears& L, const int8_t* xq, const floa
 int smallbatch_route(const FusedLinears& L, int64_t M, int64_t K);
 double smallbatch_us(const FusedLinears& L, int64_t M, int64_t K);
 // Whether a launch that would go to the prefill GEMM is faster on the small-batch kernels; rewrite: the GEMM would need its
-// weights rewritten first (TL1).
-bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite);
+// weights rewritten first (TL1); split_fits: its workspace holds the slices of a split K.
+bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite, bool split_fits = true);
 hipError_t launch_i2s_gemv1_stream(const FusedLinears& L, const float* x, int K, int8_t* xq, float* x_scale,
                                    int32_t* x_rowsum, hipStream_t stream, int fmt = kFmtI2s);
 // The TL1 weights of `count` (1..kMaxFused) N[i] x K tensors rewritten as I2_S words (same positions, N[i] K / 4

@@ -68,6 +68,14 @@ def test_small_batch_long_rows(layout, M, N, K):
     _vs_oracle(layout, M, N, K, seed=inputs.seed_for(14, 7000 + M + N + K))
 
 
+# Long rows where the split GEMM is the faster one, unless the workspace is that of one weight.
+@pytest.mark.parametrize("split_ws", [False, True], ids=["one weight's workspace", "the group's workspace"])
+def test_long_rows_fused(split_ws):
+    _announce("long rows fused", split_ws)
+    from tests.test_gpu_fused import _fused_case
+    _fused_case("i2s", 65, 44096, [256, 256], seed=inputs.seed_for(14, 7500), split_ws=split_ws)
+
+
 # The 8B-class groups at 32, 64 and 112 tokens through the fused call (the quantiser, then one launch per group).
 @pytest.mark.parametrize("layout", ["i2s", "tl1"])
 @pytest.mark.parametrize("M,K,Ns", [(32, 4096, [4096, 1024, 1024]), (112, 4096, [14336, 14336]),
