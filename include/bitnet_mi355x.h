@@ -66,7 +66,8 @@ typedef enum {
  *
  * Integer-weight layouts (Appendix "Insight", Table 3, Algorithm "ELUT mpGEMM"): weights from a set of C consecutive
  * integers, packed from int8 values with bitnet_pack_int_weights; the accumulators are the sums of the table lookups of
- * Eq. 3 (with the sign operation of Eq. 5 where the set is symmetric), formed as int8 matrix products.  Row-major planes; group j of row n is weights g j .. g j+g-1.
+ * Eq. 3 (with the sign operation of Eq. 5 where the set is symmetric), formed as int8 matrix products.  Row-major
+ * planes; group j of row n is weights g j .. g j+g-1.
  * BITNET_LAYOUT_C4G2: C = 4 {-2, -1, 0, 1}, g = 2, code 4 (w0 + 2) + (w1 + 2) in 4 bits (group j in byte
  *   n K/4 + j/2, low nibble first); 2 bits per weight.  Size N*K/4.
  * BITNET_LAYOUT_C5G2: C = 5 {-2, .., 2}, g = 2, 4-bit index |5 w0 + w1| placed as C4G2's codes, then a sign plane
@@ -155,11 +156,13 @@ size_t bitnet_mpgemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K
  *          nothing kept between calls.  Calls that run concurrently must not share it.
  *   Shapes: M >= 1, N % 16 == 0, K % 64 == 0, K <= 132096 (127 * K < 2^24 keeps acc exact in fp32);
  *   I2_S and TL1 also need N * K and M * K below 2^32.  I2_S: M <= 16 runs the decode GEMV; 17 <= M <= 112 with
- *   x_rowsum given and K <= 16384 runs the small-batch kernels (32-token tiles, or for short launches the GEMV in slices
- *   of up to 16 tokens; the regime between decode and prefill, which the paper leaves open, Sec. "Limitations"); larger
- *   M runs them where the prefill GEMM would split K and the problem is small, and the prefill GEMM otherwise.  TL1: the
- *   same kernels (the pair codes expanded to int8 in registers) where I2_S runs them; otherwise the weights are
- *   rewritten in the I2_S layout in the workspace (N * K / 4 bytes) for the prefill GEMM.
+ *   x_rowsum given and K <= 16384 runs the small-batch kernels (32-token tiles, or for few rows the GEMV in slices of
+ *   up to 16 tokens; the regime between decode and prefill, which the paper leaves open, Sec. "Limitations"); larger M
+ *   or K runs them where the prefill GEMM would split K and they are estimated to be faster, and the prefill GEMM
+ *   otherwise.  TL1: the same kernels (the pair codes expanded to int8 in registers) where I2_S runs them and, with
+ *   x_rowsum given, up to 256 tokens (224 for many rows of K <= 4096); otherwise the weights are rewritten in the I2_S
+ *   layout in the workspace (N * K / 4 bytes, asked for past 16 tokens whichever route the call takes) for the prefill
+ *   GEMM.
  *   Integer-weight layouts (C4G2, C5G2, C3G5): the group codes expanded to int8 and multiplied on int8 MFMA, up to 16
  *   tokens per slice and all slices in one launch, any M; x_rowsum is not used and no workspace is needed.  TL2_0 and
  *   TL1_0: the lossy table lookups described with the layouts (from three tokens on as one-hot products on int8 MFMA, up
@@ -216,14 +219,15 @@ size_t bitnet_mpgemm_fused_workspace_bytes(int layout, int n_linears, const int6
  *                               (bitnet_mpgemm_fused_workspace_bytes lets a prefill launch split K).
  *   Shapes: 1 <= M <= 2^24; each weight as in bitnet_mpgemm.  I2_S with M == 1 and K <= 61440 runs as one
  *   launch (every work group quantises the row itself, keeping the codes in LDS); other I2_S cases run the
- *   quantiser and then all products in one launch (the decode GEMV for M <= 16, the prefill GEMM over the
- *   weights' concatenated row tiles above).  TL2 with M == 1 and 384 <= K < 18816 also runs as one launch (the
+ *   quantiser and then all products in one launch (the decode GEMV for M <= 16, the small-batch kernels or the
+ *   prefill GEMM over the weights' concatenated row tiles above, as bitnet_mpgemm).  TL2 with M == 1 and 384 <= K < 18816 also runs as one launch (the
  *   row quantised in every work group, the triples expanded for MFMA); other TL2 cases run the quantiser and
  *   then one launch for all weights (the MFMA expansion for M <= 16 and K < 18816; for M > 16, every weight
  *   rewritten in the I2_S layout and one prefill launch, where ws holds all of them) or one bitnet_mpgemm call
- *   per weight.  TL1 runs as I2_S up to 16 tokens (the same launches, the pair codes expanded in registers) and
- *   as TL2 above (every weight rewritten in the I2_S layout, one prefill launch).  The integer-weight layouts run
- *   the quantiser inside the launch for one token, else the quantiser and one launch for every weight.
+ *   per weight.  TL1 runs as I2_S wherever that is the decode GEMV or the small-batch kernels (the same launches, the
+ *   pair codes expanded in registers) and up to 256 tokens on the small-batch kernels; past that as TL2 above (every
+ *   weight rewritten in the I2_S layout, one prefill launch).  The integer-weight and lossy layouts run the
+ *   quantiser inside the launch for one token, else the quantiser and one launch for every weight.
  */
 bitnet_status bitnet_mpgemm_fused(int layout, int n_linears, const void* const* packed, const size_t* packed_bytes,
                                   const float* const* w_scale, const int64_t* N, int64_t K, const float* x,
