@@ -539,7 +539,7 @@ size_t prefill_workspace_bytes(const FusedLinears& L, int64_t M, int64_t K) {
 
 // Where the GEMM would split K (its tiles leave half the CUs idle or more), the launch runs where the estimate is lower.
 // The GEMM's: its start and the finish pass, 1.3 us per 256-k stage of a slice, and the int32 slices (fitted to 340
-// launches, one in six off by more than 7%).  Measured, us, I2_S, GEMM / small batch: q + k + v of the 8B class at 120 and
+// launches, one in three off by more than 7%).  Measured, us, I2_S, GEMM / small batch: q + k + v of the 8B class at 120 and
 // 512 tokens 26.7 / 11.0 and 31.8 / 22.4; its down projection, K = 14336, at 256 tokens 31.7 / 25.1 and at 768 55.8 / 62.7;
 // 9024 rows of K = 26752 at 34 tokens 37.8 / 46.6, 7488 of 22720 at 67 35.5 / 42.6.  Without a split the GEMM's tiles are the
 // better ones (8640 + 8640 rows, K = 3200, at 256 tokens 25.9 / 30.3), unless the weights would be rewritten for them: TL1

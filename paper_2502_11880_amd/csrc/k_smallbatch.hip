@@ -434,8 +434,8 @@ Route tile_route(const FusedLinears& L, int64_t M, int64_t K) {
 }
 
 // Estimated times in us, each a line through what its kernel spends time on: the start, the chain of 256-k blocks, the
-// work groups on a CU, and their rounds.  Fitted to launches of 3000 shapes (17 to 112 tokens, K to 33024, 16 to 66048
-// rows, I2_S and TL1); one in six is off by more than 4 to 8%.
+// work groups on a CU, and their rounds.  Fitted to launches of 2200 shapes (17 to 1200 tokens, K to 43008, 16 to 66048
+// rows, I2_S and TL1), one in three of which is off by more than 4 to 8%; checked on 1500 others.
 double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K) {
     const double cus = device_cus(), nkb = (double)((K + kI2sBlockK - 1) / kI2sBlockK);
     const int rows = r == kTilesWide ? 128 : r == kTiles64x8 || r == kTiles64x4 ? 64 : 32;
@@ -453,8 +453,9 @@ double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K) {
 }
 
 // The GEMV's token slices as launch_i2s_decode plans them; infinite where they are no candidate: up to four blocks of K
-// (the tiles were ahead in all but one of 200 shapes) and launches whose work groups walk more than three row groups, which
-// stream, and read every word once a slice (98 tokens, 2048 -> 6144 + 6144 rows: 22.8 against 17.6).
+// (the tiles were ahead in all but four of 515 shapes, in those by 9% at most) and launches whose work groups walk more
+// than three row groups, which stream, and read every word once a slice (98 tokens, 2048 -> 6144 + 6144 rows: 14.5 against
+// 11.2).
 double slices_us(const FusedLinears& L, int64_t M, int64_t K) {
     const double never = __builtin_inf();
     if (!i2s_sliced_ok(M, K, true) || K <= 4 * kI2sBlockK) return never;
@@ -477,8 +478,8 @@ double slices_us(const FusedLinears& L, int64_t M, int64_t K) {
 
 // The GEMV's slices are the finer split (16 rows a work group, 16 waves on one row of blocks), the tiles the cheaper one per
 // word: few rows with long K go to the slices (us, slices / tiles: 64 rows of K = 11648 at 84 tokens 5.7 / 10.4; 512 of 10112
-// at 31 6.1 / 9.9; 3 x 1536 of 1536 at 112 6.8 / 7.6; 1152 of 3392 at 41 5.1 / 6.3), the rest to the tiles (4096 of 4096 at
-// 45 6.9 / 6.5; 4096 of 14336 at 45 20.0 / 12.0).  On a tie, the tiles.
+// at 31 6.1 / 9.9; 3 x 1536 of 1536 at 112 6.8 / 7.6; 1152 of 3392 at 41 5.1 / 6.3), the rest to the tiles (3840 of 3840 at
+// 45 7.1 / 6.4; 4096 of 14336 at 45 20.0 / 12.0).  On a tie, the tiles.
 Route route_of(const FusedLinears& L, int64_t M, int64_t K) {
     const Route r = tile_route(L, M, K);
     return 1.02 * slices_us(L, M, K) < tiles_us(r, L, M, K) ? kGemvSlices : r;
