@@ -547,16 +547,22 @@ size_t prefill_workspace_bytes(const FusedLinears& L, int64_t M, int64_t K) {
 // where the GEMM's second tile of tokens is full, with K <= 4096 and 80 rows a CU or more (32224 + 32224 rows of K = 1472 at
 // 253 tokens 50.9 / 60.4, 23792 + 23792 of 1664 at 248 46.7 / 50.9).
 // A split that the workspace does not hold (split_fits false) is estimated as the unsplit launch it then is.
-bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite, bool split_fits) {
-    int wn, splits;
-    prefill_plan(L, M, K, wn, splits);
-    if (rewrite && M <= 256) return splits > 1 || M <= 224 || K > 16 * kBK || total_rows(L) < 80 * (int64_t)device_cus();
+// splits: the plan's.
+static bool split_is_slower(const FusedLinears& L, int64_t M, int64_t K, bool rewrite, int splits, bool split_fits) {
     if (splits == 1) return false;
     if (!split_fits) splits = 1;
     const int64_t nkb = (K + kBK - 1) / kBK, rows = total_rows(L);
     const double gemm = 13.47 + 1.30 * (double)((nkb + splits - 1) / splits) + 0.38e-6 * 4.0 * splits * (double)(M * rows);
     const double rewritten = rewrite ? 3.0 + 0.8e-6 * (double)(rows * K / 4) : 0.0;
     return smallbatch_us(L, M, K) < gemm + rewritten;
+}
+
+bool smallbatch_beats_prefill(const FusedLinears& L, int64_t M, int64_t K, bool rewrite, bool split_fits) {
+    if (rewrite && M <= 224) return true;
+    int wn, splits;
+    prefill_plan(L, M, K, wn, splits);
+    if (rewrite && M <= 256) return splits > 1 || K > 16 * kBK || total_rows(L) < 80 * (int64_t)device_cus();
+    return split_is_slower(L, M, K, rewrite, splits, split_fits);
 }
 
 hipError_t launch_i2s_prefill(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
@@ -566,7 +572,7 @@ hipError_t launch_i2s_prefill(const FusedLinears& L, const int8_t* xq, const flo
     const int64_t ntot = total_rows(L);
     // split-K needs the token sums and the workspace for the slices
     const bool fits = ws && ws_bytes >= (size_t)splits * M * ntot * sizeof(int32_t);
-    if (x_rowsum && smallbatch_beats_prefill(L, M, K, false, fits))
+    if (x_rowsum && split_is_slower(L, M, K, false, splits, fits))
         return launch_smallbatch(L, xq, x_scale, x_rowsum, M, K, stream, kFmtI2s);
     if (!x_rowsum || !fits) splits = 1;
     int32_t* part = splits > 1 ? static_cast<int32_t*>(ws) : nullptr;

@@ -423,8 +423,7 @@ enum Route { kGemvSlices, kTiles32x4, kTiles32x8, kTiles64x8, kTiles64x4, kTiles
 //                 12.6; 8 waves 15.0, wide 12.7, GEMV 15.5)
 //   more          the wide kernel (gate + up at 45 tokens: 16.2; 64 rows 19.1, GEMV 22.7)
 // Up to four blocks of K have no work for a fifth wave: 32 rows, 4 waves.
-Route tile_route(const FusedLinears& L, int64_t M, int64_t K) {
-    const int64_t cus = device_cus();
+Route tile_route(const FusedLinears& L, int64_t M, int64_t K, int64_t cus) {
     int64_t t = 0;
     for (int i = 0; i < L.count; ++i) t += (L.N[i] + 31) / 32;
     t *= (M + kTok - 1) / kTok;
@@ -436,13 +435,13 @@ Route tile_route(const FusedLinears& L, int64_t M, int64_t K) {
 // Estimated times in us, each a line through what its kernel spends time on: the start, the chain of 256-k blocks, the
 // work groups on a CU, and their rounds.  Fitted to launches of 2200 shapes (17 to 1200 tokens, K to 43008, 16 to 66048
 // rows, I2_S and TL1), one in three of which is off by more than 4 to 8%; checked on 1500 others.
-double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K) {
-    const double cus = device_cus(), nkb = (double)((K + kI2sBlockK - 1) / kI2sBlockK);
+double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K, int64_t cus) {
+    const double nkb = (double)((K + kI2sBlockK - 1) / kI2sBlockK);
     const int rows = r == kTilesWide ? 128 : r == kTiles64x8 || r == kTiles64x4 ? 64 : 32;
     int64_t groups = 0;
     for (int i = 0; i < L.count; ++i) groups += (L.N[i] + rows - 1) / rows;
     groups *= (M + kTok - 1) / kTok;
-    const double g = (double)groups / cus;                        // work groups a CU; the wide kernel keeps two resident
+    const double g = (double)groups / (double)cus;                // work groups a CU; the wide kernel keeps two resident
     switch (r) {
         case kTiles32x4: return 3.56 + 0.10 * nkb + 0.16 * g * nkb + 0.17 * g;
         case kTiles32x8: return 3.65 + 0.14 * nkb + 0.03 * g * nkb + 0.52 * g;
@@ -456,10 +455,10 @@ double tiles_us(Route r, const FusedLinears& L, int64_t M, int64_t K) {
 // (the tiles were ahead in all but four of 515 shapes, in those by 9% at most) and launches whose work groups walk more
 // than three row groups, which stream, and read every word once a slice (98 tokens, 2048 -> 6144 + 6144 rows: 14.5 against
 // 11.2).
-double slices_us(const FusedLinears& L, int64_t M, int64_t K) {
+double slices_us(const FusedLinears& L, int64_t M, int64_t K, int64_t cus) {
     const double never = __builtin_inf();
     if (!i2s_sliced_ok(M, K, true) || K <= 4 * kI2sBlockK) return never;
-    const int64_t cus = device_cus(), nkb = (K + kI2sBlockK - 1) / kI2sBlockK;
+    const int64_t nkb = (K + kI2sBlockK - 1) / kI2sBlockK;
     const int64_t per = std::min<int64_t>(M, decode_slice_tokens(K)), slices = (M + per - 1) / per;
     const bool four = nkb <= 16 && L.total > cus / 2;             // 4-wave groups, several to a CU; else 16 waves, one
     const int64_t u = (nkb + (four ? 3 : 15)) / (four ? 4 : 16);  // blocks a wave
@@ -480,15 +479,16 @@ double slices_us(const FusedLinears& L, int64_t M, int64_t K) {
 // word: few rows with long K go to the slices (us, slices / tiles: 64 rows of K = 11648 at 84 tokens 5.7 / 10.4; 512 of 10112
 // at 31 6.1 / 9.9; 3 x 1536 of 1536 at 112 6.8 / 7.6; 1152 of 3392 at 41 5.1 / 6.3), the rest to the tiles (3840 of 3840 at
 // 45 7.1 / 6.4; 4096 of 14336 at 45 20.0 / 12.0).  On a tie, the tiles.
-Route route_of(const FusedLinears& L, int64_t M, int64_t K) {
-    const Route r = tile_route(L, M, K);
-    return 1.02 * slices_us(L, M, K) < tiles_us(r, L, M, K) ? kGemvSlices : r;
+Route route_of(const FusedLinears& L, int64_t M, int64_t K, int64_t cus) {
+    const Route r = tile_route(L, M, K, cus);
+    const double sliced = slices_us(L, M, K, cus);
+    return sliced < __builtin_inf() && 1.02 * sliced < tiles_us(r, L, M, K, cus) ? kGemvSlices : r;
 }
 
 template <int FMT>
 hipError_t launch_fmt(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum, int M,
                       int K, hipStream_t stream) {
-    switch (route_of(L, M, K)) {
+    switch (route_of(L, M, K, device_cus())) {
         case kGemvSlices: return launch_i2s_decode(L, xq, x_scale, x_rowsum, M, K, stream, FMT);
         case kTiles32x4: launch_tile<1, 4, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
         case kTiles32x8: launch_tile<1, 8, FMT>(L, xq, x_scale, x_rowsum, M, K, stream); break;
@@ -501,10 +501,11 @@ hipError_t launch_fmt(const FusedLinears& L, const int8_t* xq, const float* x_sc
 
 }  // namespace
 
-int smallbatch_route(const FusedLinears& L, int64_t M, int64_t K) { return route_of(L, M, K); }
+int smallbatch_route(const FusedLinears& L, int64_t M, int64_t K) { return route_of(L, M, K, device_cus()); }
 
 double smallbatch_us(const FusedLinears& L, int64_t M, int64_t K) {
-    return std::min(tiles_us(tile_route(L, M, K), L, M, K), slices_us(L, M, K));
+    const int64_t cus = device_cus();
+    return std::min(tiles_us(tile_route(L, M, K, cus), L, M, K, cus), slices_us(L, M, K, cus));
 }
 
 hipError_t launch_smallbatch(const FusedLinears& L, const int8_t* xq, const float* x_scale, const int32_t* x_rowsum,
